@@ -8,7 +8,7 @@ kernel).  The FP64 delay table is built once per geometry on the host, before
 the timed region.
 
 Prints one JSON line: DM-trial*samples/s, the roofline position of the
-dominant kernel (dedispersion, integer-ALU bound) from HIP events around its
+dominant kernel (dedispersion, on the matrix cores) from HIP events around its
 launches, the CPU oracle timed on a bounded sample of the same workload, and
 (after the timed region) the wall time of one GA tile search and the p50/p99
 chunk latency of a few seconds of serving.
@@ -38,6 +38,11 @@ HBM_PEAK_GBS = 8000.0
 # 1.11 x this issue rate, three-operand and packed forms 0.85-0.90 x.
 VALU_LANES_PER_CLK = 64
 ALU_PEAK_TOPS = 256 * VALU_LANES_PER_CLK * 2.4e9 * 2 / 1e12
+# Matrix cores, dense int8: 4096 multiply-adds per clock per CU (5.03 POP/s).
+# The dedispersion kernel's products select samples with 0/1 matrices: one
+# multiply-add per addition is the least (and the peak below), one per
+# remainder of the channel group, two to five on the beam, is what they take.
+MATRIX_PEAK_TOPS = 256 * 4096 * 2.4e9 / 1e12
 
 # LDS reads: 256 B/clk/CU (CDNA4 doubled CDNA3's 128) = 157.3 TB/s; measured
 # ds_read_b128 209 B/clk/CU, ds_read_b64 (the dedispersion kernel's sums) 194,
@@ -47,7 +52,7 @@ LDS_PEAK_TBS = 256 * 256 * 2.4e9 / 1e12
 METRIC = "DM-trial·samples/s per GPU + % HBM roofline; GA tune time; p99 chunk latency"
 UNIT = "DM-trial·samples/s"
 PMC_FILE = os.path.join(ROOT, "profiles", "dedisperse_beam_traffic.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_1811_04165_amd", "csrc", "dedisperse.hip")
+KERNEL_SRC = os.path.join(ROOT, "paper_1811_04165_amd", "csrc", "dedisperse_matrix.hip")
 
 
 def kernel_hash() -> str:
@@ -1284,8 +1289,13 @@ def main() -> int:
     ops = float(g.n_chan) * samples
     achieved = ops / (k1_avg / 1e3) / 1e12
     traffic = measured_traffic(ops)
-    # LDS reads: every addition reads its 16-bit sample from LDS once
-    lds_bytes = 2.0 * ops
+    # explicit tiles of other than 32 trials run on the vector units
+    matrix = tiles.dms_per_block * tiles.dms_per_thread == 32 and not tiles.direct_reads
+    alu_peak = MATRIX_PEAK_TOPS if matrix else ALU_PEAK_TOPS
+    # LDS: on the matrix cores, 32 trials x 32 channels x 64 columns stage 2 KiB,
+    # read 6 KiB of operands and add 8 KiB of results; the other kernel reads
+    # the 16-bit sample of every addition
+    lds_bytes = (0.25 if matrix else 2.0) * ops
     lds_tbs = lds_bytes / (k1_avg / 1e3) / 1e12
     # whole-path HBM bytes: input once, dd written and read once, S/N tables
     path_bytes = g.n_chan * x.stride(0) + 2 * 4 * samples + 8 * len(wl.widths) * g.n_dm
@@ -1302,8 +1312,9 @@ def main() -> int:
         "dtype": "u8", "data": "synthetic",
         "config": {"workload": wl.name, "n_chan": g.n_chan, "n_dm": g.n_dm, "n_out": wl.n_out, "n_in": n_in,
                    "widths": list(wl.widths), "tiles": tiles.as_dict(), "pulses_found": found},
-        "roofline": {"bound": "alu", "kernel": "dedisperse", "achieved": achieved, "peak": ALU_PEAK_TOPS,
-                     "unit": "TOP/s", "frac": achieved / ALU_PEAK_TOPS, "traffic": traffic,
+        "roofline": {"bound": "alu", "kernel": "dedisperse", "achieved": achieved, "peak": alu_peak,
+                     "unit": "TOP/s", "frac": achieved / alu_peak, "vector_alu_frac": achieved / ALU_PEAK_TOPS,
+                     "traffic": traffic,
                      "avg_launch_ms": k1_avg, "ops_per_launch": ops,
                      "lds": {"bytes_per_launch": lds_bytes, "achieved": lds_tbs, "peak": LDS_PEAK_TBS,
                              "unit": "TB/s", "frac": lds_tbs / LDS_PEAK_TBS}},

@@ -116,7 +116,14 @@ typedef struct {
  * The LDS footprint of the dedispersion tile must fit in 160 KiB and its
  * staging must need at most 4 items of 16 samples per work-item (3 when
  * samples_per_thread is 16, 2 when it is 32 or when it is 16 with two DMs per
- * wavefront); direct reads use no LDS. */
+ * wavefront); direct reads use no LDS.
+ *
+ * Brute-force dedispersion of 256 or more channels whose neighbours move
+ * nearly alike runs on the matrix cores, 32 DMs per work-group: always with
+ * automatic tiles, and outside a batch also with tiles of 32 DMs (dms_per_block
+ * * dms_per_thread) that stage through LDS.  Such tiles must be valid as ever;
+ * of them threads_per_dm * samples_per_thread then chooses between rows of 256
+ * samples (up to 256) and the longest that fit.  Results are the same. */
 typedef struct {
     int32_t threads_per_dm;
     int32_t samples_per_thread;

@@ -44,8 +44,6 @@
 // are widened every `flush_every` subbands, before they can overflow.
 #include "internal.h"
 
-#include <cstdlib>
-
 namespace amber {
 namespace {
 
@@ -87,24 +85,6 @@ typedef __attribute__((address_space(3))) const uint32_t lds_u1;
 __host__ __device__ constexpr uint32_t widen_sel(int a)
 {
     return (uint32_t)a | 0x0c00u | ((uint32_t)(a + 1) << 16) | 0x0c000000u;
-}
-
-// Maps the round-robin dispatch of work-groups over the 8 XCDs onto tiles so
-// that the groups one XCD runs are consecutive DM blocks of the same time tile
-// and share their input windows in that XCD's L2.
-__device__ __forceinline__ void tile_of_block(int id, int nx, int ny, int remap, int &tx, int &ty)
-{
-    if (remap) {
-        const int nb = nx * ny;
-        const int xcd = id & 7, local = id >> 3;
-        const int per = nb >> 3, rem = nb & 7;
-        const int logical = xcd * per + (xcd < rem ? xcd : rem) + local;
-        ty = logical % ny;
-        tx = logical / ny;
-    } else {
-        tx = id % nx;
-        ty = id / nx;
-    }
 }
 
 struct StageArgs {
@@ -725,12 +705,6 @@ KernelFn pick(int spt, int cu, int maxi, int u16, int dpt)
     return nullptr;
 }
 
-int xcd_remap_setting()
-{
-    const char *e = getenv("AMBER_XCD_REMAP");
-    return e ? atoi(e) : 1;
-}
-
 }  // namespace
 
 amber_status check_stage_stride(const DedispPlan &p, int64_t in_stride)
@@ -762,6 +736,7 @@ DedispJob make_dedisp_job(const DedispPlan &p, const int32_t *d_delays, int n_dm
     j.block_start = 0;
     j.flush_every = 256;
     j.groups = 1;
+    j.mat_parts = p.mat_parts;
     return j;
 }
 
@@ -791,10 +766,12 @@ amber_status launch_dedisperse(const DedispPlan &p, const int32_t *d_delays, int
     (void)n_in;
     DedispJob j = make_dedisp_job(p, d_delays, n_dm, n_chan, d_in, in_stride, d_dd, dd_stride, n_out);
     j.keep = d_keep;
-    const int64_t lds = p.lds_bytes + (d_keep ? mask_lds_bytes(p) : 0);
+    const int64_t lds = p.lds_bytes + (d_keep && !p.mat ? mask_lds_bytes(p) : 0);
     if (lds > kMaxLdsBytes)
         return fail(AMBER_E_CONFIG, "masked dedispersion tile needs %lld B of LDS (limit %lld)", (long long)lds,
                     (long long)kMaxLdsBytes);
+    if (p.mat)
+        return launch_dedisperse_matrix_jobs(p, &j, nullptr, 1, (int64_t)j.tiles_t * j.tiles_dm, lds, stream);
     return launch_dedisperse_jobs(p, &j, nullptr, 1, (int64_t)j.tiles_t * j.tiles_dm, lds, stream);
 }
 

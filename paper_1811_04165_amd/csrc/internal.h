@@ -44,6 +44,11 @@ struct DedispPlan {
     int direct;         // reads the input from global memory, no LDS staging
                         // (win, omax and maxi are then unused)
     int64_t lds_bytes;  // dynamic LDS per work-group
+    // Runs on the matrix cores (dedisperse_matrix.hip): 32 trials x tile_t
+    // samples per work-group; of the fields above only tile_t, dpb * dpt (32)
+    // and omax count then.  mat: remainders per pass (0: another kernel);
+    // mat_parts: column ranges a channel group is cut into.
+    int mat, mat_parts;
 };
 
 amber_status plan_dedisperse(const amber_tiles &t, const amber_delay_info &info, DedispPlan *out, int in_u16 = 0);
@@ -53,6 +58,23 @@ amber_status plan_dedisperse(const amber_tiles &t, const amber_delay_info &info,
 // such limit).
 constexpr int64_t kMaxStageSpan = 0xffffffffll - 64;
 amber_status check_stage_stride(const DedispPlan &p, int64_t in_stride);
+// Matrix-core kernel: trials and wavefronts per work-group (8: two per SIMD,
+// with 256 registers each; 12 with fewer measured 440 us against 394 on the
+// 1536-channel beam), and LDS bytes of a wavefront beside the sums (staged
+// columns and tables).
+constexpr int kMatRows = 32, kMatWaves = 8, kMatWaveLds = 5120;
+// Spare columns between the rows of sums: an addition is off by at most omax
+// to the left and omax + 63 to the right.
+constexpr int matrix_spare(int omax) { return (omax + 64 + 3) / 4 * 4; }
+constexpr int64_t matrix_lds_bytes(int tile_t, int omax)
+{
+    return kMatWaves * kMatWaveLds + 16 + 4ll * (matrix_spare(omax) + kMatRows * (tile_t + matrix_spare(omax)));
+}
+// Turns a staged uint8 plan into a matrix-core plan where that is the faster
+// kernel (see the rule there); automatic: the tiles are the library's choice.
+void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, DedispPlan *p);
+// 1 unless AMBER_XCD_REMAP=0: neighbouring tiles share an XCD's L2.
+int xcd_remap_setting();
 // LDS a launch with keep flags adds: the zeroed region zapped channels read
 // (64 lanes x samples_per_thread / 2 dwords).
 inline int64_t mask_lds_bytes(const DedispPlan &p) { return (int64_t)kWave * (p.spt / 2) * 4; }
@@ -113,6 +135,7 @@ struct DedispJob {
     // counts from group 0's input
     int groups, group_blocks;
     int64_t group_delays, group_in, group_out, group_keep;  // int32 elements, bytes, bytes, channels
+    int mat_parts;  // DedispPlan's, for the matrix-core kernel
 };
 
 // One beam's boxcar / S/N work (rows of job j occupy work-groups
@@ -195,6 +218,8 @@ amber_status subband_run(const int32_t *d_delay1, const int32_t *d_delay2, const
 // uint8 input, int32 sums, one problem per job (groups 1).
 amber_status launch_dedisperse_direct_jobs(const DedispPlan &p, const DedispJob *single, const DedispJob *d_jobs,
                                            int n_jobs, int64_t n_blocks, hipStream_t stream);
+amber_status launch_dedisperse_matrix_jobs(const DedispPlan &p, const DedispJob *single, const DedispJob *d_jobs,
+                                           int n_jobs, int64_t n_blocks, int64_t lds_bytes, hipStream_t stream);
 amber_status launch_dedisperse(const DedispPlan &p, const int32_t *d_delays, int n_dm, int n_chan,
                                const uint8_t *d_in, int64_t in_stride, int64_t n_in, int32_t *d_dd,
                                int64_t dd_stride, int64_t n_out, hipStream_t stream, const uint8_t *d_keep = nullptr);
@@ -216,5 +241,25 @@ amber_status launch_assemble(uint8_t *d_cur, const uint8_t *d_prev, const uint8_
 amber_status launch_integrate_snr(const BoxcarPlan &p, const amber_tiles &t, const int32_t *d_dd, int n_dm,
                                   int64_t dd_stride, int64_t n_out, const int32_t *widths, int n_widths,
                                   float *d_snr, int32_t *d_peak, hipStream_t stream, int decimate = 0);
+
+#if defined(__HIP__)
+// Maps the round-robin dispatch of work-groups over the 8 XCDs onto tiles so
+// that the groups one XCD runs are consecutive DM blocks of the same time tile
+// and share their input windows in that XCD's L2.
+__device__ __forceinline__ void tile_of_block(int id, int nx, int ny, int remap, int &tx, int &ty)
+{
+    if (remap) {
+        const int nb = nx * ny;
+        const int xcd = id & 7, local = id >> 3;
+        const int per = nb >> 3, rem = nb & 7;
+        const int logical = xcd * per + (xcd < rem ? xcd : rem) + local;
+        ty = logical % ny;
+        tx = logical / ny;
+    } else {
+        tx = id % nx;
+        ty = id / nx;
+    }
+}
+#endif
 
 }  // namespace amber

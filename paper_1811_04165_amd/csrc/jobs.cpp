@@ -9,6 +9,7 @@ namespace amber {
 void LaunchSet::add_dedisperse(const DedispPlan &p, DedispJob j)
 {
     auto it = std::find_if(d_.begin(), d_.end(), [&](const DGroup &g) {
+        if (p.mat || g.plan.mat) return g.plan.mat == p.mat && g.plan.tile_t == p.tile_t;
         return g.plan.tpd == p.tpd && g.plan.spt == p.spt && g.plan.dpb == p.dpb && g.plan.cu == p.cu &&
                g.plan.in_u16 == p.in_u16 && g.plan.dpt == p.dpt && g.plan.direct == p.direct;
     });
@@ -74,7 +75,10 @@ amber_status LaunchSet::launch(const void *d_tables, hipStream_t stream) const
     const char *p = static_cast<const char *>(d_tables);
     for (const auto &g : d_) {
         const DedispJob *tab = reinterpret_cast<const DedispJob *>(p);
-        amber_status s = g.plan.direct
+        amber_status s = g.plan.mat
+                             ? launch_dedisperse_matrix_jobs(g.plan, nullptr, tab, (int)g.jobs.size(), g.n_blocks, g.lds,
+                                                            stream)
+                         : g.plan.direct
                              ? launch_dedisperse_direct_jobs(g.plan, nullptr, tab, (int)g.jobs.size(), g.n_blocks, stream)
                              : launch_dedisperse_jobs(g.plan, nullptr, tab, (int)g.jobs.size(), g.n_blocks, g.lds,
                                                       stream);
