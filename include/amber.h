@@ -90,17 +90,15 @@ typedef struct {
  *                      of two
  *   snr_threads        work-items per work-group of the boxcar / S/N kernels
  *                      (nrThreadsD0); 64..1024, power of two.  In the fused
- *                      kernel for up to 8 sliding widths of at most 64
- *                      samples: snr_threads / 64 wavefronts share a row
+ *                      kernel for sliding widths: snr_threads / 64 wavefronts
+ *                      share a row (at most 8 with a width above 64)
  *   boxcar_step[k]     consecutive outputs per work-item for width k of the
  *                      boxcar / S/N kernels (nrItemsD0, one per width as the
  *                      paper has one per downsampling factor); 1, 2, 4 or 8.
- *                      Used by decimation, by the materialised boxcar / S/N
- *                      and by the fused kernel for more or wider widths; the
- *                      fused kernel for up to 8 sliding widths of at most 64
- *                      samples reads every width from one prefix per 4
- *                      outputs and has no such gene (the value must still be
- *                      valid)
+ *                      Used by decimation and by the materialised boxcar /
+ *                      S/N; the fused kernel for sliding widths reads every
+ *                      width from one prefix per 4 outputs and has no such
+ *                      gene (the value must still be valid)
  *   dms_per_thread     DM trials per wavefront (nrDMsPerThread): 1 or 2 (2
  *                      with samples_per_thread <= 16); 0 reads as 1.  A
  *                      work-group covers dms_per_block * dms_per_thread DMs,
@@ -351,15 +349,12 @@ amber_status amber_snr(const int32_t *d_box, int32_t n_dm, int64_t box_stride, i
  * smoothing and S/N kernels after dedispersion): each dedispersed row is read
  * once and its boxcar series live only in LDS and registers.  Same arguments
  * and results as the pair, without d_box.
- * Up to 8 sliding widths of at most 64 samples (rows below 2^29 samples) take
- * a kernel in which the work-group's wavefronts sweep consecutive spans of
- * the row: per 256 outputs a prefix in LDS, per width the maximum, the block
- * where it first rises and an exact int64 sum of squares; the mean follows
- * from the row's sum in closed form.  Its results are exact (up to the FP64
- * finish) for dd >= 0 with dd * max(widths) < 2^31 (any dedispersed uint8
- * data), and for signed dd with |dd| * max(widths) < 2^30; a row whose values
- * could overflow the int64 sums has them recomputed in FP64.  More or wider
- * widths take the chunked kernel of amber_integrate.
+ * Rows below 2^29 samples take a kernel in which the work-group's wavefronts
+ * sweep consecutive spans of the row: per 256 outputs a prefix in LDS, per
+ * width the maximum, the block where it first rises and an exact 64-bit sum of
+ * squares; the mean follows from the row's sum in closed form.  A width whose
+ * values could overflow these sums has its statistics recomputed in int64 and
+ * FP64.  Longer rows take the chunked kernel of amber_integrate.
  * tiles == NULL: the defaults, with snr_threads 64 when n_dm >= 4096 (with
  * that many rows one wavefront per row keeps the CUs busiest) and the default
  * 128 below, raised while 16 * snr_threads < twice the largest width rounded

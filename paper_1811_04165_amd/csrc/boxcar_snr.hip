@@ -25,6 +25,7 @@
 // tested per element only in a work-item's last, partial step.
 #include "internal.h"
 
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 #include <type_traits>
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(MAXT) void integrate_snr_kernel(BoxJob single, cons
     }
 }
 
-// ---- fused boxcar + S/N over wavefront spans (sliding widths <= 64) --------
+// ---- fused boxcar + S/N over wavefront spans (sliding widths) -------------
 //
 // One work-group per dedispersed row and W = blockDim / 64 wavefronts.  The
 // row's outputs are cut into blocks of 256 (64 lanes x 4); wavefront v sweeps
@@ -377,26 +378,47 @@ __global__ __launch_bounds__(MAXT) void integrate_snr_kernel(BoxJob single, cons
 //  - per width it keeps the running maximum (3-input maxima of its 4 values),
 //    the block where that maximum last rose, and the sum of squares in int64
 //    (one 32 x 32 + 64-bit multiply-add per value).
-// The int64 sums are exact while (max width x max |centred sample|)^2 times
-// the values per lane stays below 2^62, and the wavefront's block totals
-// (which give the row's sum) while max |centred sample| < 2^23; each
-// wavefront tracks its largest centred sample, and a row that breaks either
-// bound has its sum and sums of squares recomputed after the sweep (no
-// dedispersed uint8 data of fewer than 32 896 channels comes near it).  The sum of box' over the row needs no per-output work: it is w T
-// minus head and tail terms, with T the centred row's sum.  After the sweep:
-// wavefront reductions, one barrier, then per width one wavefront finds the
-// first index of the maximum (its 4 candidate outputs in the earliest block
-// that reaches it, recomputed from dd), forms the mean from the closed form,
-// the variance and the S/N.
+// A boxcar fits int32 while width x max |centred sample| does, a lane's sum of
+// squares 64 bits while its square times the values per lane does, and a
+// block's total int32 while max |centred sample| < 2^23; each wavefront tracks
+// its largest centred sample, and a width that breaks a bound has its
+// statistics recomputed after the sweep (no dedispersed uint8 data of fewer
+// than 32 896 channels comes near it at 64 samples).  The sum of box' over the
+// row needs no per-output work: it is w T minus head and tail terms, with T the
+// centred row's sum.  After the sweep: wavefront reductions, one barrier, then
+// per width one wavefront finds the first index of the maximum (its 4 candidate
+// outputs in the earliest block that reaches it differ by the samples that
+// enter and leave), forms the mean from the closed form, the variance and the
+// S/N.
+//
+// Two forms.  Narrow (LOOK = 1): widths to 64, a window ends in the next block
+// at the latest, 592 dwords of LDS per wavefront.  Wide (LOOK = 4): widths to
+// 1024, 8 KiB, indices masked.  Both are bound by vector issue (about 3 per
+// width and sample).  The wide form, us, with 11 widths 1 .. 1024 in place of
+// two passes over LDS chunks with FP64 sums per output: 1024 rows x 24576
+// samples 236 -> 60, 2048 x 12208 177 -> 65, 256 x 8192 74 -> 26; 10 uneven
+// widths to 999: 297 -> 92, 219 -> 78, 89 -> 39.  10 widths to 24 take 84 as two
+// narrow passes and 128 as one wide one, so the wide form is for widths above
+// 64, and for more than 8 widths of a table of beams (which has no passes).
 
 constexpr int kSpanBlk = 256;
 constexpr int kSpanMaxW = 64;
+constexpr int kSpanWideW = 1024;
 #ifndef SPAN_NB
 #define SPAN_NB 4
 #endif
 // reads of an odd block reach 256 + 4 * 63 + kSpanMaxW + 7 = 579 < 2 * 256 + kSpanDup
 constexpr int kSpanDup = 80;
 constexpr int kSpanRing = 2 * kSpanBlk + kSpanDup;  // dwords per wavefront
+// The wide form (LOOK = 4): a window of up to 1024 samples ends in one of the
+// four blocks after its own, so the ring holds 8 and its indices are masked.
+constexpr int kSpanWideRing = 8 * kSpanBlk;
+
+template <int LOOK>
+__device__ __forceinline__ const u32x4 *span_at(const uint32_t *ring, int i)
+{
+    return reinterpret_cast<const u32x4 *>(ring + (LOOK == 1 ? i : i & (kSpanWideRing - 1)));
+}
 
 struct SpanRes {
     long long key;
@@ -474,57 +496,52 @@ __device__ __forceinline__ int32_t min3i(int32_t a, int32_t b, int32_t c)
 }
 
 // Centres block `blk` on c, writes its prefix (starting at `base`) to ring
-// slot blk & 1, widens [xlo, xhi] to its centred samples and returns the
+// slot blk & 1, widens [xlo, xhi] to its samples and returns the
 // block's total (uint32, true value fits int32).
-template <bool VEC>
+template <bool VEC, int LOOK>
 __device__ __forceinline__ uint32_t span_put(uint32_t *ring, int blk, const i32x4 &r, const int32_t *__restrict__ row,
                                              int n_out, int32_t c, uint32_t base, int lane, int32_t &xlo,
                                              int32_t &xhi)
 {
     const int t = blk * kSpanBlk + 4 * lane;
-    int32_t x[4];
+    uint32_t x[4];
+    auto take = [&](int32_t v0, int32_t v1, int32_t v2, int32_t v3) {
+        xlo = min3i(min3i(xlo, v0, v1), v2, v3);
+        xhi = max3i(max3i(xhi, v0, v1), v2, v3);
+        x[0] = (uint32_t)v0 - (uint32_t)c; x[1] = (uint32_t)v1 - (uint32_t)c;
+        x[2] = (uint32_t)v2 - (uint32_t)c; x[3] = (uint32_t)v3 - (uint32_t)c;
+    };
     if (VEC && (blk + 1) * kSpanBlk <= n_out) {  // the whole block lies in the row
-        x[0] = r.x - c; x[1] = r.y - c; x[2] = r.z - c; x[3] = r.w - c;
+        take(r.x, r.y, r.z, r.w);
     } else if (VEC) {
         if (t + 4 <= n_out) {
-            x[0] = r.x - c; x[1] = r.y - c; x[2] = r.z - c; x[3] = r.w - c;
+            take(r.x, r.y, r.z, r.w);
         } else {
+            int32_t v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = (t + e < n_out) ? ((g_i32 *)row)[t + e] - c : 0;
+            for (int e = 0; e < 4; ++e) v[e] = (t + e < n_out) ? ((g_i32 *)row)[t + e] : c;
+            take(v[0], v[1], v[2], v[3]);
         }
     } else {
-        const int32_t v[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = (t + e < n_out) ? v[e] - c : 0;
+        take(t < n_out ? r.x : c, t + 1 < n_out ? r.y : c, t + 2 < n_out ? r.z : c, t + 3 < n_out ? r.w : c);
     }
-    xlo = min3i(min3i(xlo, x[0], x[1]), x[2], x[3]);
-    xhi = max3i(max3i(xhi, x[0], x[1]), x[2], x[3]);
-    const uint32_t l0 = (uint32_t)x[0], l1 = l0 + (uint32_t)x[1], l2 = l1 + (uint32_t)x[2],
-                   l3 = l2 + (uint32_t)x[3];
+    const uint32_t l0 = x[0], l1 = l0 + x[1], l2 = l1 + x[2], l3 = l2 + x[3];
     const uint32_t incl = wave_scan_incl(l3);
     const uint32_t ex = incl - l3 + base;
     const u32x4 q = u32x4{ex, ex + l0, ex + l1, ex + l2};
-    const int slot = blk & 1;
+    const int slot = blk & (LOOK == 1 ? 1 : 7);
     *reinterpret_cast<u32x4 *>(ring + slot * kSpanBlk + 4 * lane) = q;
-    if (slot == 0 && lane < kSpanDup / 4) *reinterpret_cast<u32x4 *>(ring + 2 * kSpanBlk + 4 * lane) = q;
+    if (LOOK == 1 && slot == 0 && lane < kSpanDup / 4) *reinterpret_cast<u32x4 *>(ring + 2 * kSpanBlk + 4 * lane) = q;
     return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
 }
 
-// box'[e] = Q[b + e + w] - Q[b + e] for the lane's 4 outputs (A = Q[b .. b + 3]).
+// box'[e] = Q[b + e + w] - Q[b + e] for the lane's 4 outputs: A = Q[b .. b + 3],
+// g = Q[b + w - R ..], R = w & 3.
 template <int R>
-__device__ __forceinline__ void span_box(const uint32_t *ring, int b, int w, const u32x4 &A, int32_t (&x)[4])
+__device__ __forceinline__ void span_box(const uint32_t (&g)[8], const u32x4 &A, int32_t (&x)[4])
 {
-    const int q = w - R;
-    const u32x4 g0 = *reinterpret_cast<const u32x4 *>(ring + b + q);
-    if (R == 0) {
-        x[0] = (int32_t)(g0.x - A.x); x[1] = (int32_t)(g0.y - A.y);
-        x[2] = (int32_t)(g0.z - A.z); x[3] = (int32_t)(g0.w - A.w);
-    } else {
-        const u32x4 g1 = *reinterpret_cast<const u32x4 *>(ring + b + q + 4);
-        const uint32_t g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-        x[0] = (int32_t)(g[R] - A.x); x[1] = (int32_t)(g[R + 1] - A.y);
-        x[2] = (int32_t)(g[R + 2] - A.z); x[3] = (int32_t)(g[R + 3] - A.w);
-    }
+    x[0] = (int32_t)(g[R] - A.x); x[1] = (int32_t)(g[R + 1] - A.y);
+    x[2] = (int32_t)(g[R + 2] - A.z); x[3] = (int32_t)(g[R + 3] - A.w);
 }
 
 template <bool POW2>
@@ -560,11 +577,11 @@ __device__ __forceinline__ void span_acc(const int32_t (&x)[4], int t0, int n_va
 
 // The statistics of block j for every width (its prefix and the next
 // block's are in the ring).
-template <int NW, bool POW2, bool TAIL>
+template <int NW, bool POW2, bool TAIL, int LOOK>
 __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane, const WidthSet &ws, int n_out,
                                            int32_t (&vmax)[NW], int32_t (&jmax)[NW], long long (&s2)[NW])
 {
-    const int b = (j & 1) * kSpanBlk + 4 * lane;
+    const int b = (j & (LOOK == 1 ? 1 : 7)) * kSpanBlk + 4 * lane;
     const int t0 = j * kSpanBlk + 4 * lane;
     if (POW2) {
         // widths 1, 2, 4, ..: every window end lies in one of the groups of
@@ -574,7 +591,7 @@ __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane
         constexpr int NG = NW < 3 ? 2 : NW - 1;
         u32x4 G[NG];
 #pragma unroll
-        for (int g = 0; g < NG; ++g) G[g] = *reinterpret_cast<const u32x4 *>(ring + b + (g == 0 ? 0 : 2 << g));
+        for (int g = 0; g < NG; ++g) G[g] = *span_at<LOOK>(ring, b + (g == 0 ? 0 : 2 << g));
         __builtin_amdgcn_sched_barrier(0);
         const u32x4 A = G[0];
         const uint32_t lo[8] = {G[0].x, G[0].y, G[0].z, G[0].w, G[1].x, G[1].y, G[1].z, G[1].w};
@@ -595,17 +612,34 @@ __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane
         return;
     }
     const u32x4 A = *reinterpret_cast<const u32x4 *>(ring + b);
+    // four widths' reads at a time, all before the first use, as above (a read
+    // that only one of four remainders does without costs less than a wait)
 #pragma unroll
-    for (int k = 0; k < NW; ++k) {
-        const int w = span_width<POW2>(ws, k);
-        int32_t x[4];
-        switch (w & 3) {
-        case 0: span_box<0>(ring, b, w, A, x); break;
-        case 1: span_box<1>(ring, b, w, A, x); break;
-        case 2: span_box<2>(ring, b, w, A, x); break;
-        default: span_box<3>(ring, b, w, A, x); break;
+    for (int k0 = 0; k0 < NW; k0 += 4) {
+        if (LOOK > 1 && k0 >= ws.n) break;  // (the wide form is compiled for several counts at once)
+        u32x4 lo[4], hi[4];
+#pragma unroll
+        for (int q = 0; q < 4 && k0 + q < NW; ++q) {
+            const int at = b + (span_width<POW2>(ws, k0 + q) & ~3);
+            lo[q] = *span_at<LOOK>(ring, at);
+            hi[q] = *span_at<LOOK>(ring, at + 4);
         }
-        span_acc<TAIL>(x, t0, n_out - w + 1, vmax[k], jmax[k], s2[k], j);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4 && k0 + q < NW; ++q) {
+            const int k = k0 + q;
+            if (LOOK > 1 && k >= ws.n) break;
+            const int w = span_width<POW2>(ws, k);
+            const uint32_t g[8] = {lo[q].x, lo[q].y, lo[q].z, lo[q].w, hi[q].x, hi[q].y, hi[q].z, hi[q].w};
+            int32_t x[4];
+            switch (w & 3) {
+            case 0: span_box<0>(g, A, x); break;
+            case 1: span_box<1>(g, A, x); break;
+            case 2: span_box<2>(g, A, x); break;
+            default: span_box<3>(g, A, x); break;
+            }
+            span_acc<TAIL>(x, t0, n_out - w + 1, vmax[k], jmax[k], s2[k], j);
+        }
     }
 }
 
@@ -666,20 +700,22 @@ __device__ __forceinline__ long long wave_sum_ll(long long v)
     return (long long)lane63((uint64_t)v);
 }
 
-// NW: the exact number of widths; POW2: widths are 1, 2, 4, ... 2^(NW-1).
+// NW: the number of widths (LOOK = 4 without POW2: at least); POW2: widths are
+// 1, 2, 4, ... 2^(NW-1).  LOOK: blocks after its own that a window may end in.
 constexpr int NB = SPAN_NB;
-template <int NW, bool POW2, bool VEC>
-__global__ __launch_bounds__(1024) void span_snr_kernel(BoxJob single, const BoxJob *__restrict__ jobs, int n_jobs,
+template <int NW, bool POW2, bool VEC, int LOOK>
+__global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob single, const BoxJob *__restrict__ jobs, int n_jobs,
                                                         WidthSet ws)
 {
     extern __shared__ uint4 lds4[];
     // the wavefront index is uniform: keep it (and the span bounds, the block
     // counter and every branch on them) in scalar registers
     const int W = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    uint32_t *ring = reinterpret_cast<uint32_t *>(lds4) + wave * kSpanRing;
-    SpanRes *res = reinterpret_cast<SpanRes *>(reinterpret_cast<uint32_t *>(lds4) + W * kSpanRing);
+    constexpr int kRing = LOOK == 1 ? kSpanRing : kSpanWideRing;
+    uint32_t *ring = reinterpret_cast<uint32_t *>(lds4) + wave * kRing;
+    SpanRes *res = reinterpret_cast<SpanRes *>(reinterpret_cast<uint32_t *>(lds4) + W * kRing);
     long long *tres = reinterpret_cast<long long *>(res + W * NW);
-    int *flags = reinterpret_cast<int *>(tres + W);  // per wavefront: its sums of squares may have overflowed
+    long long *peaks = tres + W;  // per wavefront: its largest centred sample
 
     int i = blockIdx.x;
     BoxJob job = single;
@@ -699,7 +735,8 @@ __global__ __launch_bounds__(1024) void span_snr_kernel(BoxJob single, const Box
     const int32_t tail = n_out - 1 - lane >= 0 ? ((g_i32 *)row)[n_out - 1 - lane] : 0;
     int maxw = 1;
 #pragma unroll
-    for (int k = 0; k < NW; ++k) maxw = max(maxw, span_width<POW2>(ws, k));
+    for (int k = 0; k < NW; ++k)
+        if (LOOK == 1 || k < ws.n) maxw = max(maxw, span_width<POW2>(ws, k));
     const int n_min = n_out - maxw + 1;  // outputs below it are valid for every width
 
     int32_t vmax[NW], jmax[NW];
@@ -711,20 +748,32 @@ __global__ __launch_bounds__(1024) void span_snr_kernel(BoxJob single, const Box
         s2[k] = 0;
     }
     long long tsum = 0;
-    int32_t xlo = 0, xhi = 0;
-    bool overflow = false;
+    int32_t xlo = c, xhi = c;
 
     const int nb = (n_out + kSpanBlk - 1) / kSpanBlk;
     const int jb = (int)((uint32_t)nb * (uint32_t)wave / (uint32_t)W),
               je = (int)((uint32_t)nb * (uint32_t)(wave + 1) / (uint32_t)W);
     if (jb < je) {
         // blocks before j_tail have every output valid for every width; the
-        // others (at most two, at the row's end) take the masked statistics
+        // others (at most LOOK + 1, at the row's end) take the masked statistics
         const int j_tail = min(max(n_min / kSpanBlk, jb), je);
         uint32_t base = 0;
+        auto put = [&](int blk, const i32x4 &x) {
+            const uint32_t tot = span_put<VEC, LOOK>(ring, blk, x, row, n_out, c, base, lane, xlo, xhi);
+            base += tot;
+            if (blk >= jb && blk < je) tsum += (int32_t)tot;
+        };
+        // the first LOOK blocks from j on, loaded together
+        auto begin = [&](int j) {
+            i32x4 first[LOOK];
+#pragma unroll
+            for (int m = 0; m < LOOK; ++m) first[m] = span_load<VEC>(rs, max(j + m, 0), lane);
+#pragma unroll
+            for (int m = 0; m < LOOK; ++m) put(j + m, first[m]);
+        };
         // Main part, blocks [jb, j_tail): NB block buffers.  While block j
-        // is summed, blocks j + 1 (its windows' lookahead, put into the ring
-        // first) .. j + NB - 1 are loaded and j + NB is being loaded.  The
+        // is summed, blocks to j + LOOK (its windows' lookahead, put into the
+        // ring first) are there and the NB - 1 after it are being loaded.  The
         // loop is unrolled NB times so that buffers are never copied (a copy
         // would wait for the load in flight); it starts NB - 1 steps early at
         // most (dummy steps: loads and prefix writes of earlier blocks, no
@@ -734,82 +783,66 @@ __global__ __launch_bounds__(1024) void span_snr_kernel(BoxJob single, const Box
             int j = jb - r;
             i32x4 buf[NB];
 #pragma unroll
-            for (int u = 0; u < NB; ++u) buf[u] = span_load<VEC>(rs, max(j + u, 0), lane);
-            base = span_put<VEC>(ring, j, buf[0], row, n_out, c, 0u, lane, xlo, xhi);
-            if (j >= jb) tsum += (int32_t)base;
+            for (int u = 1; u < NB; ++u) buf[u] = span_load<VEC>(rs, max(j + LOOK - 1 + u, 0), lane);
+            begin(j);
             for (; j < j_tail; j += NB) {
 #pragma unroll
                 for (int u = 0; u < NB; ++u) {
                     const int jj = j + u;
                     // blocks past the lookahead are loaded and never used
                     // (past the row's end the loads return zeros)
-                    buf[u] = span_load<VEC>(rs, max(jj + NB, 0), lane);
-                    const uint32_t tot =
-                        span_put<VEC>(ring, jj + 1, buf[(u + 1) % NB], row, n_out, c, base, lane, xlo, xhi);
-                    base += tot;
-                    if (jj + 1 >= jb && jj + 1 < je) tsum += (int32_t)tot;
+                    buf[u] = span_load<VEC>(rs, max(jj + LOOK - 1 + NB, 0), lane);
+                    put(jj + LOOK, buf[(u + 1) % NB]);
                     wave_sync_lds();
-                    if (jj >= jb) span_block<NW, POW2, false>(ring, jj, lane, ws, n_out, vmax, jmax, s2);
+                    if (jj >= jb) span_block<NW, POW2, false, LOOK>(ring, jj, lane, ws, n_out, vmax, jmax, s2);
                     wave_sync_lds();
                 }
             }
         } else {
-            base = span_put<VEC>(ring, jb, span_load<VEC>(rs, jb, lane), row, n_out, c, 0u, lane, xlo,
-                                 xhi);
-            tsum += (int32_t)base;
+            begin(jb);
         }
-        // tail blocks: block j + 1 loaded and put, then block j's masked statistics
+        // tail blocks: the last lookahead block loaded and put, then block
+        // j's masked statistics
         for (int j = j_tail; j < je; ++j) {
-            const uint32_t tot = span_put<VEC>(ring, j + 1, span_load<VEC>(rs, j + 1, lane), row, n_out, c,
-                                               base, lane, xlo, xhi);
-            base += tot;
-            if (j + 1 < je) tsum += (int32_t)tot;
+            put(j + LOOK, span_load<VEC>(rs, j + LOOK, lane));
             wave_sync_lds();
-            span_block<NW, POW2, true>(ring, j, lane, ws, n_out, vmax, jmax, s2);
+            span_block<NW, POW2, true, LOOK>(ring, j, lane, ws, n_out, vmax, jmax, s2);
             wave_sync_lds();
         }
-        // exactness: a block's total (256 centred samples) fits int32 while
-        // max |x'| < 2^23; the int64 sums of squares while (maxw max |x'|)^2
-        // times the 4 (je - jb) values per lane and width stays below 2^62
-        const int32_t xm = (int32_t)wave_max_ll((long long)max(max(xhi, -xlo), 0));
-        const double bound = (double)maxw * (double)xm;
-        overflow = xm >= (1 << 23) || bound * bound * (4.0 * (double)(je - jb)) >= 4.6e18;
     }
+    // the largest centred sample (of this wavefront's)
+    long long xmax = wave_max_ll(max((long long)xhi - c, (long long)c - xlo));
 
     // wavefront totals: per width (max, earliest 4-output group) and sum of squares
 #pragma unroll
     for (int k = 0; k < NW; ++k) {
+        if (LOOK > 1 && k >= ws.n) break;
         const int u0 = jmax[k] >= 0 ? jmax[k] * kSpanBlk + 4 * lane : 0;
         const long long key = wave_max_ll(pack_key(vmax[k], u0));
-        const double s = wave_sum_d((double)s2[k]);
+        const double s = wave_sum_d((double)(unsigned long long)s2[k]);
         if (lane == 0) res[wave * NW + k] = SpanRes{key, s};
     }
     if (lane == 0) {
         tres[wave] = tsum;
-        flags[wave] = overflow ? 1 : 0;
+        peaks[wave] = xmax;
     }
     __syncthreads();
-    bool redo = false;
     long long T = 0;
     for (int v = 0; v < W; ++v) {
-        redo = redo || flags[v] != 0;
+        xmax = max(xmax, peaks[v]);
         T += tres[v];
-    }
-    if (redo) {
-        // the centred row's sum again, in int64
-        long long a = 0;
-        for (int t = lane; t < n_out; t += 64) a += (long long)row[t] - c;
-        T = wave_sum_ll(a);
     }
     // this wavefront's widths k = wave, wave + W, ..: totals over the
     // wavefronts (in a fixed order), then the loads that find the first index
-    // of each maximum, all issued before any is used
+    // of each maximum among outputs u0 .. u0 + 3 (the samples that enter and
+    // leave from one to the next), all issued before any is used
+    const int blocks = (nb + W - 1) / W;
     long long key[NW];
     double s2t[NW];
-    int32_t v1[NW], v2[NW];
+    int32_t edge[NW];
 #pragma unroll
     for (int k = 0; k < NW; ++k) {
-        if (k % W != wave) continue;
+        if (k % W != wave || (LOOK > 1 && k >= ws.n)) continue;
         key[k] = LLONG_MIN;
         s2t[k] = 0.0;
         for (int v = 0; v < W; ++v) {
@@ -818,66 +851,85 @@ __global__ __launch_bounds__(1024) void span_snr_kernel(BoxJob single, const Box
             s2t[k] += r.s2;
         }
         const int u0 = (int)(0xffffffffu - (uint32_t)(key[k] & 0xffffffffll));
-        v1[k] = (u0 + lane < n_out) ? row[u0 + lane] : 0;
-        v2[k] = (lane < 3 && u0 + 64 + lane < n_out) ? row[u0 + 64 + lane] : 0;
+        const int at = u0 + (lane < 3 ? lane : span_width<POW2>(ws, k) + lane - 3);
+        edge[k] = (lane < 6 && at < n_out) ? row[at] : 0;
     }
 #pragma unroll
     for (int k = 0; k < NW; ++k) {
-        if (k % W != wave) continue;
+        if (k % W != wave || (LOOK > 1 && k >= ws.n)) continue;
         const int w = span_width<POW2>(ws, k);
         const int N = n_out - w + 1;
-        double s = s2t[k];
-        if (redo) {
-            // sums of squares again in FP64: lane l takes a contiguous run
-            // of outputs and slides its window along it
+        double vm = (double)(int32_t)(key[k] >> 32);
+        int tstar = (int)(0xffffffffu - (uint32_t)(key[k] & 0xffffffffll));
+        double s1, s = s2t[k];
+        // Exact: a block's total (256 centred samples) and a boxcar fit int32,
+        // and a lane's sum of squares (at most 4 values a block) 64 bits.
+        const double bound = (double)w * (double)xmax;
+        if (xmax < (1 << 23) && bound < 2147483647.0 && bound * bound * (4.0 * (double)blocks) < 1.8e19) {
+            // the boxcar sum's weights below w: its head's and tail's samples
+            double corr = 0.0;
+            auto ends = [&](int m, int32_t xh, int32_t xt) {
+                const int th = m, tt = n_out - 1 - m;
+                if (th < n_out) {
+                    const int cnt = min(th, N - 1) - max(0, th - w + 1) + 1;
+                    corr += (double)(w - cnt) * (double)(xh - c);
+                }
+                if (tt >= w - 1) {
+                    const int cnt = min(tt, N - 1) - max(0, tt - w + 1) + 1;
+                    corr += (double)(w - cnt) * (double)(xt - c);
+                }
+            };
+            if (lane <= w - 2) ends(lane, head, tail);
+            if (LOOK > 1) {
+                // (w <= n_out: both indices lie in the row)
+                for (int m = 64 + lane; m <= w - 2; m += 64) ends(m, row[m], row[n_out - 1 - m]);
+            }
+            corr = wave_sum_d(corr);
+            s1 = (double)w * (double)T - corr;
+            // box[u0 + e] - box[u0], and the first e of the largest
+            long long d = 0, best = 0;
+            const int u0 = tstar;
+#pragma unroll
+            for (int e = 1; e < 4; ++e) {
+                d += (long long)__builtin_amdgcn_readlane(edge[k], e + 2) - __builtin_amdgcn_readlane(edge[k], e - 1);
+                if (u0 + e < N && d > best) {
+                    best = d;
+                    tstar = u0 + e;
+                }
+            }
+        } else {
+            // any samples: lane l takes a contiguous run of outputs and slides
+            // its window along it, in int64 and FP64
             const int C = (N + 63) / 64, t0 = lane * C, t1 = min(N, t0 + C);
-            double acc = 0.0;
+            long long top = LLONG_MIN;
+            int at = 0x7fffffff;
+            double a1 = 0.0, a2 = 0.0;
             if (t0 < t1) {
                 long long bx = 0;
                 for (int m = 0; m < w; ++m) bx += (long long)row[t0 + m] - c;
-                acc = (double)bx * (double)bx;
-                for (int t = t0 + 1; t < t1; ++t) {
+                for (int t = t0;;) {
+                    if (bx > top) {
+                        top = bx;
+                        at = t;
+                    }
+                    a1 += (double)bx;
+                    a2 += (double)bx * (double)bx;
+                    if (++t >= t1) break;
                     bx += (long long)row[t + w - 1] - (long long)row[t - 1];
-                    acc += (double)bx * (double)bx;
                 }
             }
-            s = wave_sum_d(acc);
+            const long long most = wave_max_ll(top);
+            tstar = -(int)wave_max_ll(top == most ? -(long long)at : LLONG_MIN);
+            s1 = wave_sum_d(a1);
+            s = wave_sum_d(a2);
+            vm = (double)most;
         }
-        const int32_t vm = (int32_t)(key[k] >> 32);
-        const int u0 = (int)(0xffffffffu - (uint32_t)(key[k] & 0xffffffffll));
-        // head and tail outputs of the boxcar sum's weights below w
-        double corr = 0.0;
-        if (lane <= w - 2) {
-            const int th = lane, tt = n_out - 1 - lane;
-            if (th < n_out) {
-                const int cnt = min(th, N - 1) - max(0, th - w + 1) + 1;
-                corr += (double)(w - cnt) * (double)(head - c);
-            }
-            if (tt >= w - 1) {
-                const int cnt = min(tt, N - 1) - max(0, tt - w + 1) + 1;
-                corr += (double)(w - cnt) * (double)(tail - c);
-            }
-        }
-        corr = wave_sum_d(corr);
-        const double s1 = (double)w * (double)T - corr;
-        // first index of the maximum among outputs u0 .. u0 + 3
-        const uint32_t p1 = wave_scan_incl((uint32_t)v1[k]), p2 = wave_scan_incl((uint32_t)v2[k]);
-        const uint32_t p64 = (uint32_t)__builtin_amdgcn_readlane((int)p1, 63);
-        auto S = [&](int m) -> uint32_t {
-            if (m == 0) return 0u;
-            if (m <= 64) return (uint32_t)__builtin_amdgcn_readlane((int)p1, m - 1);
-            return p64 + (uint32_t)__builtin_amdgcn_readlane((int)p2, m - 65);
-        };
-        const uint32_t want = (uint32_t)vm + (uint32_t)w * (uint32_t)c;
-        int tstar = u0;
-        for (int e = 3; e >= 0; --e)
-            if (u0 + e < N && S(e + w) - S(e) == want) tstar = u0 + e;
         if (lane == 0) {
             const double m1 = s1 / (double)N;
             double var = s / (double)N - m1 * m1;
             var = var > 0.0 ? var : 0.0;
             const double sigma = sqrt(var);
-            job.snr[(size_t)k * job.n_dm + i] = sigma > 0.0 ? (float)(((double)vm - m1) / sigma) : 0.0f;
+            job.snr[(size_t)k * job.n_dm + i] = sigma > 0.0 ? (float)((vm - m1) / sigma) : 0.0f;
             if (job.peak) job.peak[(size_t)k * job.n_dm + i] = tstar;
         }
     }
@@ -996,22 +1048,27 @@ BoxJob make_box_job(const int32_t *d_dd, int n_dm, int64_t dd_stride, int64_t n_
 
 namespace {
 
-// The span kernel: sliding widths up to kSpanMaxW, at most 8 per launch.
-template <int NW>
-void launch_span_nw(bool pow2, bool vec, dim3 grid, dim3 block, size_t lds, hipStream_t stream, const BoxJob &one,
+template <int NW, int LOOK>
+amber_status launch_span_nw(bool pow2, bool vec, dim3 grid, dim3 block, size_t lds, hipStream_t stream, const BoxJob &one,
                     const BoxJob *d_jobs, int n_jobs, const WidthSet &ws)
 {
-    if (pow2) {
-        if (vec) hipLaunchKernelGGL((span_snr_kernel<NW, true, true>), grid, block, lds, stream, one, d_jobs, n_jobs, ws);
-        else hipLaunchKernelGGL((span_snr_kernel<NW, true, false>), grid, block, lds, stream, one, d_jobs, n_jobs, ws);
-    } else {
-        if (vec) hipLaunchKernelGGL((span_snr_kernel<NW, false, true>), grid, block, lds, stream, one, d_jobs, n_jobs, ws);
-        else hipLaunchKernelGGL((span_snr_kernel<NW, false, false>), grid, block, lds, stream, one, d_jobs, n_jobs, ws);
-    }
+    auto go = [&](auto kernel) -> amber_status {
+        amber_status s = allow_lds(kernel, (int64_t)lds, "hipFuncSetAttribute(integrate_snr, span)");
+        if (s == AMBER_OK) hipLaunchKernelGGL(kernel, grid, block, lds, stream, one, d_jobs, n_jobs, ws);
+        return s;
+    };
+    if constexpr (LOOK == 1 || (NW > 7 && NW < 12))
+        if (pow2) return vec ? go(span_snr_kernel<NW, true, true, LOOK>) : go(span_snr_kernel<NW, true, false, LOOK>);
+    if constexpr (LOOK == 1 || NW % 4 == 0)
+        return vec ? go(span_snr_kernel<NW, false, true, LOOK>) : go(span_snr_kernel<NW, false, false, LOOK>);
+    return fail(AMBER_E_CONFIG, "no span kernel for %d widths", NW);
 }
 
+// The span kernel: at most 8 sliding widths up to kSpanMaxW per launch, or up
+// to kSpanWideW in its wide form.
 amber_status launch_span_snr(const BoxcarPlan &p, const BoxJob *single, const BoxJob *d_jobs, int n_jobs,
-                             int64_t n_rows, const int32_t *widths, int n_widths, bool vec, hipStream_t stream)
+                             int64_t n_rows, const int32_t *widths, int n_widths, bool wide, bool vec,
+                             hipStream_t stream)
 {
     WidthSet ws{};
     bool pow2 = true;
@@ -1020,22 +1077,31 @@ amber_status launch_span_snr(const BoxcarPlan &p, const BoxJob *single, const Bo
         pow2 = pow2 && widths[k] == (1 << k);
     }
     ws.n = n_widths;
-    const int W = p.threads / kWave;
-    const size_t lds = (size_t)W * kSpanRing * 4 + (size_t)W * n_widths * sizeof(SpanRes) +
-                       (size_t)W * sizeof(long long) + (size_t)W * sizeof(int);
+    // the wide form is compiled for exact counts of powers of two, and for
+    // counts up to 4, 8, 12 or 16 of any widths
+    const int nw = !wide || pow2 ? n_widths : (n_widths + 3) / 4 * 4;
+    const int threads = wide && p.threads > 512 ? 512 : p.threads;
+    const int W = threads / kWave;
+    const size_t lds = (size_t)W * (wide ? kSpanWideRing : kSpanRing) * 4 + (size_t)W * nw * sizeof(SpanRes) +
+                       2 * (size_t)W * sizeof(long long);
     const BoxJob one = single ? *single : BoxJob{};
-    const dim3 grid((unsigned)n_rows), block(p.threads);
-    switch (n_widths) {
-    case 1: launch_span_nw<1>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 2: launch_span_nw<2>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 3: launch_span_nw<3>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 4: launch_span_nw<4>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 5: launch_span_nw<5>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 6: launch_span_nw<6>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 7: launch_span_nw<7>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    case 8: launch_span_nw<8>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break;
-    default: return fail(AMBER_E_CONFIG, "span kernel takes 1 to 8 widths, got %d", n_widths);
+    const dim3 grid((unsigned)n_rows), block(threads);
+    amber_status s = AMBER_OK;
+#define SPAN(NW, LOOK) \
+    case NW: s = launch_span_nw<NW, LOOK>(pow2, vec, grid, block, lds, stream, one, d_jobs, n_jobs, ws); break
+    if (wide) {
+        switch (nw) {
+            SPAN(4, 4); SPAN(8, 4); SPAN(9, 4); SPAN(10, 4); SPAN(11, 4); SPAN(12, 4); SPAN(16, 4);
+        default: return fail(AMBER_E_CONFIG, "span kernel (wide) takes 1 to 16 widths, got %d", n_widths);
+        }
+    } else {
+        switch (nw) {
+            SPAN(1, 1); SPAN(2, 1); SPAN(3, 1); SPAN(4, 1); SPAN(5, 1); SPAN(6, 1); SPAN(7, 1); SPAN(8, 1);
+        default: return fail(AMBER_E_CONFIG, "span kernel takes 1 to 8 widths, got %d", n_widths);
+        }
     }
+#undef SPAN
+    if (s != AMBER_OK) return s;
     AMBER_HIP(hipGetLastError(), "integrate_snr (span) launch");
     return AMBER_OK;
 }
@@ -1050,6 +1116,14 @@ bool span_snr_applies(const int32_t *widths, int n_widths, int decimate, int64_t
     return true;
 }
 
+bool span_wide_applies(const int32_t *widths, int n_widths, int decimate, int64_t max_n_out)
+{
+    if (decimate || n_widths < 1 || n_widths > 16 || max_n_out >= ((int64_t)1 << 29)) return false;
+    for (int k = 0; k < n_widths; ++k)
+        if (widths[k] > kSpanWideW) return false;
+    return true;
+}
+
 amber_status launch_integrate_snr_jobs(const BoxcarPlan &p, const amber_tiles &t, const BoxJob *single,
                                        const BoxJob *d_jobs, int n_jobs, int64_t n_rows, const int32_t *widths,
                                        int n_widths, hipStream_t stream, int decimate, int all_vec,
@@ -1058,9 +1132,13 @@ amber_status launch_integrate_snr_jobs(const BoxcarPlan &p, const amber_tiles &t
     amber_status s = check_chunk(p);
     if (s != AMBER_OK) return s;
     if (n_rows > 0x7fffffff) return fail(AMBER_E_SHAPE, "too many rows (%lld)", (long long)n_rows);
-    if (span_snr_applies(widths, n_widths, decimate, single ? single->n_out : max_n_out)) {
+    const int64_t longest = single ? single->n_out : max_n_out;
+    const bool narrow = span_snr_applies(widths, n_widths, decimate, longest);
+    // (one beam with more than 8 widths up to 64 takes passes of 8, below)
+    const bool split = single && n_widths > 8 && *std::max_element(widths, widths + n_widths) <= kSpanMaxW;
+    if (narrow || (!split && span_wide_applies(widths, n_widths, decimate, longest))) {
         const bool vec = single ? single->vec_ok != 0 : all_vec > 0;
-        return launch_span_snr(p, single, d_jobs, n_jobs, n_rows, widths, n_widths, vec, stream);
+        return launch_span_snr(p, single, d_jobs, n_jobs, n_rows, widths, n_widths, !narrow, vec, stream);
     }
     // One beam with more than 8 series: passes of at most 8 series through
     // the 8-series kernel (each pass re-reads the rows, but the statistics of

@@ -164,6 +164,8 @@ amber_status launch_integrate_snr_jobs(const BoxcarPlan &p, const amber_tiles &t
 // Sliding widths and rows that the span kernel serves (at most 8 widths,
 // each <= 64; rows of fewer than 2^29 samples).
 bool span_snr_applies(const int32_t *widths, int n_widths, int decimate, int64_t max_n_out);
+// The same for its wide form: up to 16 sliding widths up to 1024.
+bool span_wide_applies(const int32_t *widths, int n_widths, int decimate, int64_t max_n_out);
 
 // Jobs of several beams grouped into as few launches as their launch shapes
 // allow.  Dedispersion jobs with the same tile genes share a launch (the
