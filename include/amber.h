@@ -388,6 +388,9 @@ amber_status amber_downsample(const int32_t *d_dd, int32_t n_dm, int64_t dd_stri
  *     snr[k][i] = (max y - mean) / std (population), or 0 when std == 0,
  *     peak_t[k][i] = smallest j with y_j == max y   (in downsampled samples).
  * Factor 1 is the S/N of the series itself.  FP64 moments as in amber_snr.
+ * snr_threads / 64 wavefronts (at most 8) share a row, each sweeping a span of
+ * it once for all factors (rows of 2^29 samples or more: the chunks of
+ * amber_downsample); tiles == NULL chooses them by the number of rows.
  * d_snr: device float [n_factors][n_dm]; d_peak_t: int32 [n_factors][n_dm] or
  * NULL.  Errors as amber_integrate_snr. */
 amber_status amber_downsample_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_stride, int64_t n_out,

@@ -51,6 +51,19 @@ amber_status hip_fail(hipError_t err, const char *what)
     return fail(AMBER_E_DEVICE, "%s: %s", what, hipGetErrorString(err));
 }
 
+int row_threads(int64_t rows)
+{
+    // 2560 wavefronts or more keep the CUs' loads in flight; more per
+    // row than that cost more at the row's end than they bring.  Decimated S/N,
+    // ladder of 10 factors, us at 64 / 128 / 256 / 512: 256 rows x 8192 samples
+    // 30 / 20 / 15 / 15, 771 x 9001 35 / 25 / 23 / 35, 1024 x 24576
+    // 85 / 53 / 42 / 51, 2048 x 12208 53 / 40 / 47 / 70, 8192 x 4096
+    // 56 / 67 / 91 / 194.
+    int t = rows >= 4096 ? 64 : 128;
+    while (t < 512 && rows * (t / kWave) < 2560) t *= 2;
+    return t;
+}
+
 int auto_snr_threads(int64_t rows, const int32_t *widths, int n_widths)
 {
     // measured on 12 208-sample rows, widths 1..64: 2048 rows 0.105 ms at 128
@@ -506,6 +519,7 @@ amber_status amber_downsample_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_
     if ((s = downsample_tiles(tiles, factors, n_factors, &t)) != AMBER_OK) return s;
     BoxcarPlan plan;
     if ((s = plan_boxcar(t, factors, n_factors, n_out, &plan, kMaxFactor)) != AMBER_OK) return s;
+    if (!tiles) plan.dec_threads = row_threads(n_dm);
     return launch_integrate_snr(plan, t, d_dd, n_dm, dd_stride, n_out, factors, n_factors, d_snr, d_peak,
                                 (hipStream_t)stream, 1);
 }

@@ -29,6 +29,7 @@
 #include <cfloat>
 #include <climits>
 #include <type_traits>
+#include <utility>
 
 namespace amber {
 namespace {
@@ -616,7 +617,7 @@ __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane
     // that only one of four remainders does without costs less than a wait)
 #pragma unroll
     for (int k0 = 0; k0 < NW; k0 += 4) {
-        if (LOOK > 1 && k0 >= ws.n) break;  // (the wide form is compiled for several counts at once)
+        if (LOOK > 1 && k0 >= ws.n) continue;  // (the wide form is compiled for several counts at once)
         u32x4 lo[4], hi[4];
 #pragma unroll
         for (int q = 0; q < 4 && k0 + q < NW; ++q) {
@@ -628,7 +629,7 @@ __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane
 #pragma unroll
         for (int q = 0; q < 4 && k0 + q < NW; ++q) {
             const int k = k0 + q;
-            if (LOOK > 1 && k >= ws.n) break;
+            if (LOOK > 1 && k >= ws.n) continue;
             const int w = span_width<POW2>(ws, k);
             const uint32_t g[8] = {lo[q].x, lo[q].y, lo[q].z, lo[q].w, hi[q].x, hi[q].y, hi[q].z, hi[q].w};
             int32_t x[4];
@@ -687,17 +688,6 @@ __device__ __forceinline__ double wave_sum_d(double v)
     v = add(v, dpp64<0x142, 0xa>(bits(v), 0));
     v = add(v, dpp64<0x143, 0xc>(bits(v), 0));
     return __longlong_as_double((long long)lane63(bits(v)));
-}
-
-__device__ __forceinline__ long long wave_sum_ll(long long v)
-{
-    v += (long long)dpp64<0xb1, 0xf>((uint64_t)v, 0);
-    v += (long long)dpp64<0x4e, 0xf>((uint64_t)v, 0);
-    v += (long long)dpp64<0x141, 0xf>((uint64_t)v, 0);
-    v += (long long)dpp64<0x140, 0xf>((uint64_t)v, 0);
-    v += (long long)dpp64<0x142, 0xa>((uint64_t)v, 0);
-    v += (long long)dpp64<0x143, 0xc>((uint64_t)v, 0);
-    return (long long)lane63((uint64_t)v);
 }
 
 // NW: the number of widths (LOOK = 4 without POW2: at least); POW2: widths are
@@ -816,7 +806,7 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
     // wavefront totals: per width (max, earliest 4-output group) and sum of squares
 #pragma unroll
     for (int k = 0; k < NW; ++k) {
-        if (LOOK > 1 && k >= ws.n) break;
+        if (LOOK > 1 && k >= ws.n) continue;
         const int u0 = jmax[k] >= 0 ? jmax[k] * kSpanBlk + 4 * lane : 0;
         const long long key = wave_max_ll(pack_key(vmax[k], u0));
         const double s = wave_sum_d((double)(unsigned long long)s2[k]);
@@ -932,6 +922,262 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
             job.snr[(size_t)k * job.n_dm + i] = sigma > 0.0 ? (float)((vm - m1) / sigma) : 0.0f;
             if (job.peak) job.peak[(size_t)k * job.n_dm + i] = tstar;
         }
+    }
+}
+
+// ---- decimated series and their S/N over wavefront spans --------------------
+//
+// One work-group per dedispersed row; its wavefronts take consecutive spans of
+// whole chunks of 1024 samples and sweep them without a barrier.  Per chunk: 4
+// blocks of 256 samples (loaded one chunk ahead, 16 B per lane) are prefix-
+// summed across the wavefront and written to LDS, the prefix running on over
+// the span (uint32, modulo 2^32).  A bin of factor f is the difference of the
+// prefix at two neighbouring multiples of f; the one before the chunk's first
+// was kept in LDS.  Factor 1 (every sample a bin) takes its values from the
+// loaded registers.  A span's samples before its first multiple of f and from
+// its last one on are parts of bins that cross spans: they are put together at
+// the end, where the work-group's statistics are.  So no sample is read twice
+// and any factor needs the same LDS.
+//
+// 2048 x 12208 samples, ladder 1, 10, 20, .. 3200: 213 -> 40 us (before: two
+// passes over chunks overlapping by the largest factor, three barriers each).
+// The 100 MB alone take 20 us, which factors 1 or 10 by themselves meet; each
+// further factor adds 2 us of vector issue and LDS latency, in iterations that
+// have few bins and in the reduction.
+constexpr int kDecBlocks = 4;
+constexpr int kDecChunk = kDecBlocks * kSpanBlk;
+
+// What a wavefront leaves of one factor.
+struct DecRes {
+    Stat st;        // its peak in samples
+    uint32_t head;  // the samples before its first boundary
+    uint32_t pad;
+};
+
+// Statistics in the form that the reduction moves between lanes.
+struct DecStat {
+    int32_t v;    // maximum
+    uint32_t nt;  // ~(its first sample)
+    double s1, s2;
+};
+
+__device__ __forceinline__ void dec_merge(DecStat &a, const DecStat &b)
+{
+    const long long ka = (long long)(((uint64_t)(uint32_t)a.v << 32) | a.nt),
+                    kb = (long long)(((uint64_t)(uint32_t)b.v << 32) | b.nt);
+    const bool up = kb > ka;
+    a.v = up ? b.v : a.v;
+    a.nt = up ? b.nt : a.nt;
+    a.s1 += b.s1;
+    a.s2 += b.s2;
+}
+
+// f(x, y) on the dwords of two statistics.
+template <typename F>
+__device__ __forceinline__ void dec_dwords(DecStat &a, DecStat &b, F f)
+{
+    auto both = [&](double &x, double &y) {
+        uint64_t p = (uint64_t)__double_as_longlong(x), q = (uint64_t)__double_as_longlong(y);
+        uint32_t pl = (uint32_t)p, ph = (uint32_t)(p >> 32), ql = (uint32_t)q, qh = (uint32_t)(q >> 32);
+        f(pl, ql);
+        f(ph, qh);
+        x = __longlong_as_double((long long)(((uint64_t)ph << 32) | pl));
+        y = __longlong_as_double((long long)(((uint64_t)qh << 32) | ql));
+    };
+    uint32_t av = (uint32_t)a.v, bv = (uint32_t)b.v;
+    f(av, bv);
+    a.v = (int32_t)av;
+    b.v = (int32_t)bv;
+    f(a.nt, b.nt);
+    both(a.s1, b.s1);
+    both(a.s2, b.s2);
+}
+
+// One step of the reduction within rows of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ void dec_step(DecStat &a)
+{
+    DecStat b = a;
+    dec_dwords(a, b, [](uint32_t &, uint32_t &y) {
+        y = (uint32_t)__builtin_amdgcn_update_dpp((int)y, (int)y, CTRL, 0xf, 0xf, false);
+    });
+    dec_merge(a, b);
+}
+
+template <bool VEC>
+__device__ __forceinline__ void dec_load(__amdgpu_buffer_rsrc_t rs, int s0, int n_out, int lane,
+                                         i32x4 (&x)[kDecBlocks])
+{
+#pragma unroll
+    for (int q = 0; q < kDecBlocks; ++q) {
+        const int blk = s0 / kSpanBlk + q;
+        // (a 16-byte load that straddles the row's end would return nothing)
+        if (VEC && (blk + 1) * kSpanBlk <= n_out)
+            x[q] = span_load<true>(rs, blk, lane);
+        else
+            x[q] = span_load<false>(rs, blk, lane);
+    }
+}
+
+// f(K) for K = 0 .. N - 1 as constants (a loop of this size is not always
+// unrolled, and the statistics it indexes would then live in memory).
+template <typename F, int... K>
+__device__ __forceinline__ void each_of(F f, std::integer_sequence<int, K...>)
+{
+    (f(std::integral_constant<int, K>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each(F f)
+{
+    each_of(f, std::make_integer_sequence<int, N>{});
+}
+
+// NW: at least the number of factors, a multiple of 4.  A factor 1 comes first;
+// step[k] is factor k's place in the results.
+template <int NW, bool VEC>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NW <= 12 ? 4 : 2))) void dec_snr_kernel(BoxJob job, WidthSet ws)
+{
+    extern __shared__ uint4 lds4[];
+    const int W = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    uint32_t *P = reinterpret_cast<uint32_t *>(lds4) + wave * (kDecChunk + AMBER_MAX_WIDTHS);
+    uint32_t *last = P + kDecChunk;  // per factor: the prefix at the last boundary passed
+    DecRes *res = reinterpret_cast<DecRes *>(reinterpret_cast<uint32_t *>(lds4) + W * (kDecChunk + AMBER_MAX_WIDTHS));
+    uint32_t *total = reinterpret_cast<uint32_t *>(res + W * NW);  // the spans' sums
+    const int i = blockIdx.x, n_out = (int)job.n_out;
+    const int32_t *__restrict__ row = job.dd + (size_t)i * job.dd_stride;
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, n_out);
+    const double c = (double)*(g_i32 *)row;
+    const int chunks = (n_out + kDecChunk - 1) / kDecChunk;
+    const int s_begin = (int)((int64_t)chunks * wave / W) * kDecChunk,
+              s_end = (int)((int64_t)chunks * (wave + 1) / W) * kDecChunk;
+
+    Run st[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) run_init(st[k]);
+    const bool one = ws.w[0] == 1;
+    int at[NW];  // each factor's next boundary
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        const int f = k < ws.n ? ws.w[k] : 1;
+        at[k] = (s_begin + f - 1) / f * f;
+    }
+    if (lane < NW) last[lane] = 0;
+    uint32_t base = 0;
+    i32x4 x[kDecBlocks];
+    if (s_begin < s_end) dec_load<VEC>(rs, s_begin, n_out, lane, x);
+    for (int s0 = s_begin; s0 < s_end; s0 += kDecChunk) {
+        wave_sync_lds();
+#pragma unroll
+        for (int q = 0; q < kDecBlocks; ++q) {
+            const uint32_t l0 = (uint32_t)x[q].x, l1 = l0 + (uint32_t)x[q].y, l2 = l1 + (uint32_t)x[q].z,
+                           l3 = l2 + (uint32_t)x[q].w;
+            const uint32_t incl = wave_scan_incl(l3);
+            const uint32_t ex = incl - l3 + base;
+            *reinterpret_cast<u32x4 *>(P + q * kSpanBlk + 4 * lane) = u32x4{ex, ex + l0, ex + l1, ex + l2};
+            base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+        if (one) {
+#pragma unroll
+            for (int q = 0; q < kDecBlocks; ++q) {
+                const int t = s0 + q * kSpanBlk + 4 * lane;
+                const int32_t v[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+                if (s0 + (q + 1) * kSpanBlk <= n_out) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) run_add(st[0], v[e], (uint32_t)(t + e), c);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (t + e < n_out) run_add(st[0], v[e], (uint32_t)(t + e), c);
+                }
+            }
+        }
+        // (the registers are free: the next chunk's loads; past the span they
+        // are never used, past the row they return zeros)
+        dec_load<VEC>(rs, s0 + kDecChunk, n_out, lane, x);
+        wave_sync_lds();
+        each<NW>([&](auto K) {
+            constexpr int k = K;
+            if (k >= ws.n || (k == 0 && one)) return;
+            const int f = ws.w[k];
+            while (at[k] < s0 + kDecChunk && at[k] <= n_out) {
+                // boundaries at[k] + lane f of this chunk; the bin that ends there
+                const int b = at[k] + lane * f;
+                const bool in = b < s0 + kDecChunk && b <= n_out;
+                const uint32_t end = in ? P[b - s0] : 0u;
+                const uint32_t from = !in || b - f < s0 ? last[k] : P[b - f - s0];
+                const int n = (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(in));
+                // (the span's first boundary ends another span's bin, or none)
+                if (in && b - f >= s_begin) run_add(st[k], (int32_t)(end - from), (uint32_t)(b - f), c * f);
+                if (lane == n - 1) last[k] = end;
+                if (b < s_begin + f && in) res[wave * NW + k].head = end;
+                at[k] += n * f;
+                wave_sync_lds();
+            }
+        });
+    }
+    // Two steps halve the number of statistics each, by exchanging halves of two
+    // of them at a time; the third holds factor 4 a + 2 (row & 1) + (row >> 1)
+    // in each row of 16 lanes.  (Reduced one by one they took twice the sweep.)
+    DecStat d[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) d[k] = DecStat{st[k].vmax, ~st[k].tmax, st[k].s1, st[k].s2};
+    each<NW / 2>([&](auto M) {
+        dec_dwords(d[2 * M], d[2 * M + 1], [](uint32_t &x, uint32_t &y) {
+            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            x = r[0];
+            y = r[1];
+        });
+        dec_merge(d[2 * M], d[2 * M + 1]);
+    });
+    each<NW / 4>([&](auto A) {
+        DecStat &t = d[4 * A];
+        dec_dwords(t, d[4 * A + 2], [](uint32_t &x, uint32_t &y) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            x = r[0];
+            y = r[1];
+        });
+        dec_merge(t, d[4 * A + 2]);
+        dec_step<0xb1>(t);   // quad_perm [1,0,3,2]
+        dec_step<0x4e>(t);   // quad_perm [2,3,0,1]
+        dec_step<0x141>(t);  // row_half_mirror
+        dec_step<0x140>(t);  // row_mirror
+        const int r = lane >> 4;
+        if ((lane & 15) == 0)
+            res[wave * NW + 4 * A + 2 * (r & 1) + (r >> 1)].st =
+                Stat{(long long)(((uint64_t)(uint32_t)t.v << 32) | t.nt), t.s1, t.s2};
+    });
+    if (lane == 0) total[wave] = base;
+    __syncthreads();
+    const int k = threadIdx.x;
+    if (k < ws.n) {
+        const int f = ws.w[k];
+        const double r = c * f;
+        Stat tot;
+        stat_init(tot);
+        uint32_t open = 0;  // the samples so far of the bin that crosses into the next span
+        for (int v = 0; v < W; ++v) {
+            const DecRes &q = res[v * NW + k];
+            tot.key = q.st.key > tot.key ? q.st.key : tot.key;
+            tot.s1 += q.st.s1;
+            tot.s2 += q.st.s2;
+            if (k == 0 && one) continue;
+            const int vb = (int)((int64_t)chunks * v / W) * kDecChunk, ve = (int)((int64_t)chunks * (v + 1) / W) * kDecChunk;
+            const int b = (vb + f - 1) / f * f;  // the span's first boundary
+            if (b < ve && b <= n_out) {
+                open += q.head;
+                if (b > 0) stat_add(tot, (int32_t)open, b - f, r);
+                open = total[v] - (reinterpret_cast<uint32_t *>(lds4) + v * (kDecChunk + AMBER_MAX_WIDTHS) + kDecChunk)[k];
+            } else {
+                open += total[v];
+            }
+        }
+        // the last boundary is the end of the last chunk: no span has it
+        if (!(k == 0 && one) && n_out % kDecChunk == 0 && n_out % f == 0) stat_add(tot, (int32_t)open, n_out - f, r);
+        // (peaks so far in samples)
+        const uint32_t t = 0xffffffffu - (uint32_t)(tot.key & 0xffffffffll);
+        tot.key = pack_key((int32_t)(tot.key >> 32), t / (uint32_t)f);
+        const size_t out = (size_t)ws.step[k] * job.n_dm + i;
+        finish(tot, n_out / f, r, job.snr + out, job.peak ? job.peak + out : nullptr);
     }
 }
 
@@ -1106,6 +1352,38 @@ amber_status launch_span_snr(const BoxcarPlan &p, const BoxJob *single, const Bo
     return AMBER_OK;
 }
 
+amber_status launch_dec_snr(const BoxcarPlan &p, const BoxJob &job, int64_t n_rows, const int32_t *factors, int n,
+                            hipStream_t stream)
+{
+    WidthSet ws{};
+    ws.n = n;
+    for (int k = 0; k < n; ++k) {
+        ws.w[k] = factors[k];
+        ws.step[k] = k;
+    }
+    const int one = (int)(std::find(factors, factors + n, 1) - factors);
+    if (one < n) {
+        std::swap(ws.w[0], ws.w[one]);
+        std::swap(ws.step[0], ws.step[one]);
+    }
+    const int threads = p.dec_threads ? p.dec_threads : (p.threads < 512 ? p.threads : 512), W = threads / kWave;
+    const int nw = n <= 4 ? 4 : n <= 8 ? 8 : n <= 12 ? 12 : 16;
+    const size_t lds = (size_t)W * (kDecChunk + AMBER_MAX_WIDTHS) * 4 + (size_t)W * (nw * sizeof(DecRes) + 4);
+    auto go = [&](auto vec, auto any) -> amber_status {
+        const auto kernel = job.vec_ok ? vec : any;
+        amber_status s = allow_lds(kernel, (int64_t)lds, "hipFuncSetAttribute(downsample_snr)");
+        if (s == AMBER_OK) hipLaunchKernelGGL(kernel, dim3((unsigned)n_rows), dim3(threads), lds, stream, job, ws);
+        return s;
+    };
+    amber_status s = nw == 4    ? go(dec_snr_kernel<4, true>, dec_snr_kernel<4, false>)
+                     : nw == 8  ? go(dec_snr_kernel<8, true>, dec_snr_kernel<8, false>)
+                     : nw == 12 ? go(dec_snr_kernel<12, true>, dec_snr_kernel<12, false>)
+                                : go(dec_snr_kernel<16, true>, dec_snr_kernel<16, false>);
+    if (s != AMBER_OK) return s;
+    AMBER_HIP(hipGetLastError(), "downsample_snr launch");
+    return AMBER_OK;
+}
+
 }  // namespace
 
 bool span_snr_applies(const int32_t *widths, int n_widths, int decimate, int64_t max_n_out)
@@ -1140,6 +1418,8 @@ amber_status launch_integrate_snr_jobs(const BoxcarPlan &p, const amber_tiles &t
         const bool vec = single ? single->vec_ok != 0 : all_vec > 0;
         return launch_span_snr(p, single, d_jobs, n_jobs, n_rows, widths, n_widths, !narrow, vec, stream);
     }
+    if (decimate && single && longest < ((int64_t)1 << 29))
+        return launch_dec_snr(p, *single, n_rows, widths, n_widths, stream);
     // One beam with more than 8 series: passes of at most 8 series through
     // the 8-series kernel (each pass re-reads the rows, but the statistics of
     // 16 series per work-item need registers enough to halve the resident

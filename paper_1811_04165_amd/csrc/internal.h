@@ -100,6 +100,7 @@ struct BoxcarPlan {
     int chunk;     // outputs per LDS chunk (threads * 16)
     int maxw;      // largest width
     int64_t lds_bytes;
+    int dec_threads;    // work-items per row of the decimated S/N (0: threads, at most 512)
 };
 
 // max_width: 1024 for sliding widths, 4096 for decimation factors
@@ -111,6 +112,8 @@ const amber_tiles &default_tiles();
 // tiles: 64 from 4096 rows up (one row per work-group: enough rows keep the
 // CUs busy with single-wave groups), else the default 128; raised while a
 // chunk of 16 samples per work-item is shorter than twice the largest width.
+// Work-items per row for kernels whose wavefronts share a row.
+int row_threads(int64_t rows);
 int auto_snr_threads(int64_t rows, const int32_t *widths, int n_widths);
 
 // One beam's dedispersion work: the arguments of a launch, or one entry of a
