@@ -356,9 +356,9 @@ amber_status amber_snr(const int32_t *d_box, int32_t n_dm, int64_t box_stride, i
  * values could overflow these sums has its statistics recomputed in int64 and
  * FP64.  Longer rows take the chunked kernel of amber_integrate.
  * tiles == NULL: the defaults, with snr_threads 64 when n_dm >= 4096 (with
- * that many rows one wavefront per row keeps the CUs busiest) and the default
- * 128 below, raised while 16 * snr_threads < twice the largest width rounded
- * up to 16.  A batch with automatic tiles applies the same rule to its total
+ * that many rows one wavefront per row keeps the CUs busiest), else 128,
+ * doubled up to 512 while all rows have fewer than 2560 wavefronts, and raised
+ * while 16 * snr_threads < twice the largest width rounded up to 16.  A batch with automatic tiles applies the same rule to its total
  * number of rows. */
 amber_status amber_integrate_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_stride, int64_t n_out,
                                  const int32_t *widths, int32_t n_widths,

@@ -66,10 +66,11 @@ int row_threads(int64_t rows)
 
 int auto_snr_threads(int64_t rows, const int32_t *widths, int n_widths)
 {
-    // measured on 12 208-sample rows, widths 1..64: 2048 rows 0.105 ms at 128
-    // vs 0.114 ms at 64; 8192 rows 0.325 vs 0.376 ms; 49 152 rows 1.72 vs
-    // 2.02 ms (64 vs 128)
-    int t = rows >= 4096 ? 64 : default_tiles().snr_threads;
+    // row_threads' rule; sliding widths 1 .. 64, us at 128 / 256 / 512:
+    // 256 rows x 8192 samples 16 / 13 / 13, 771 x 9001 21 / 21 / 25,
+    // 1024 x 24576 38 / 34 / 38, 2048 x 12208 36 / 39 / 51; widths 1 .. 1024:
+    // 26 / 20 / 19, 36 / 35 / 44, 60 / 58 / 66, 65 / 70 / 94
+    int t = row_threads(rows);
     int maxw = 1;
     for (int k = 0; k < n_widths; ++k) maxw = widths[k] > maxw ? widths[k] : maxw;
     const int halo = (maxw + 15) / 16 * 16;
