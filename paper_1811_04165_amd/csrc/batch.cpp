@@ -88,7 +88,7 @@ amber_status amber_batch_create(const amber_beam *beams, int32_t n_beams, const 
         if (s == AMBER_OK) s = plan_dedisperse(t, bm.info, &dp);
         if (s == AMBER_OK) s = check_stage_stride(dp, bm.in_stride);
         // (beams given one tile set stay one launch)
-        if (s == AMBER_OK && !tiles) use_matrix(bm.info, bm.in_stride, bm.n_out, true, &dp);
+        if (s == AMBER_OK && !tiles) use_matrix(bm.info, bm.in_stride, bm.n_out, true, false, &dp);
         if (s == AMBER_OK) s = plan_boxcar(t, widths, n_widths, bm.n_out, &bp);
         if (s != AMBER_OK) {
             delete b;

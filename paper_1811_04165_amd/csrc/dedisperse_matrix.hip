@@ -645,7 +645,8 @@ int xcd_remap_setting()
 //
 // so: 256 channels or more, and `most` up to 18.  (`most` is an estimate from
 // the table's summary that only the speed depends on.)
-void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, DedispPlan *p)
+void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, bool alone,
+                DedispPlan *p)
 {
     if (p->in_u16 || p->direct || n_out < 1) return;
     if (!automatic && p->dpb * p->dpt != kRows) return;  // explicit tiles choose the trials per work-group
@@ -663,16 +664,33 @@ void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, 
     // remainders per pass: more take registers (and reads) that a band with
     // fewer does not need; one pass of 12 takes less than two of 7
     const int mat = most < 5.1 ? 5 : most < 7.1 ? 7 : most < 9.1 ? 9 : 12;
-    // The longest row that the LDS holds: a work-group's delays and a pass's
-    // start count once per row, and 32 * omax spare columns come with any
-    // length.  Shorter rows where the chip would not be filled.
-    int T = 640;
-    if (!automatic && p->tile_t <= 256) T = 256;
+    // Row length.  A work-group fills a CU, so a launch takes rounds of 256; in
+    // each it takes the time of about T + omax / 2 columns plus its delays',
+    // passes' and last step's, about 400 columns' more.  The length with the
+    // least of both: rounds that are full, and otherwise the longest that the
+    // LDS holds.  (With T = 640 throughout, 1024 trials x 6104 samples were 320
+    // work-groups, and took 1280 columns' time where two rounds of 384 do.)
+    // Rows of a batch share rounds with the other beams'.
     const int64_t dms = (info.n_dm + kRows - 1) / kRows;
-    while (T > 128 && (matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes ||
-                       (automatic && dms * ((n_out + T - 1) / T) < 256)))
-        T -= 128;
-    if (matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes) return;
+    int T = 0;
+    if (!automatic && p->tile_t <= 256) {
+        T = 256;
+    } else if (!alone) {
+        T = 640;
+        while (T > 128 && (matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes || dms * ((n_out + T - 1) / T) < 256)) T -= 128;
+    } else {
+        int64_t best = 0;
+        for (int t = 128; matrix_lds_bytes(t, (int)omax) <= kMaxLdsBytes; t += 8) {
+            const int64_t rounds = (dms * ((n_out + t - 1) / t) + 255) / 256;
+            const int64_t cost = rounds * (t + omax / 2 + 400);
+            if (T == 0 || cost < best) {
+                best = cost;
+                T = t;
+            }
+            if (t >= n_out) break;
+        }
+    }
+    if (T == 0 || matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes) return;
     p->mat = mat;
     p->omax = (int)omax;
     p->dpb = 16;
