@@ -690,6 +690,115 @@ __device__ __forceinline__ double wave_sum_d(double v)
     return __longlong_as_double((long long)lane63(bits(v)));
 }
 
+// f(K) for K = 0 .. N - 1 as constants (a loop of this size is not always
+// unrolled, and the statistics it indexes would then live in memory).
+template <typename F, int... K>
+__device__ __forceinline__ void each_of(F f, std::integer_sequence<int, K...>)
+{
+    (f(std::integral_constant<int, K>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each(F f)
+{
+    each_of(f, std::make_integer_sequence<int, N>{});
+}
+
+// Statistics in the form that reductions move between lanes: the maximum, ~(its
+// first sample), and sums.
+struct DecStat {
+    int32_t v;
+    uint32_t nt;
+    double s1, s2;
+};
+struct SpanStat {
+    int32_t v;
+    uint32_t nt;
+    double s2;
+};
+
+template <typename S>
+__device__ __forceinline__ long long lane_key(const S &a)
+{
+    return (long long)(((uint64_t)(uint32_t)a.v << 32) | a.nt);
+}
+
+template <typename S>
+__device__ __forceinline__ void merge_max(S &a, const S &b)
+{
+    const bool up = lane_key(b) > lane_key(a);
+    a.v = up ? b.v : a.v;
+    a.nt = up ? b.nt : a.nt;
+}
+__device__ __forceinline__ void merge(DecStat &a, const DecStat &b)
+{
+    merge_max(a, b);
+    a.s1 += b.s1;
+    a.s2 += b.s2;
+}
+__device__ __forceinline__ void merge(SpanStat &a, const SpanStat &b)
+{
+    merge_max(a, b);
+    a.s2 += b.s2;
+}
+
+// f(x, y) on the dwords of two statistics.
+template <typename S, typename F>
+__device__ __forceinline__ void dwords(S &a, S &b, F f)
+{
+    struct D {
+        uint32_t w[sizeof(S) / 4];
+    };
+    D x = __builtin_bit_cast(D, a), y = __builtin_bit_cast(D, b);
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(S) / 4; ++i) f(x.w[i], y.w[i]);
+    a = __builtin_bit_cast(S, x);
+    b = __builtin_bit_cast(S, y);
+}
+
+// One step of the reduction within rows of 16 lanes.
+template <int CTRL, typename S>
+__device__ __forceinline__ void row_step(S &a)
+{
+    S b = a;
+    dwords(a, b, [](uint32_t &, uint32_t &y) {
+        y = (uint32_t)__builtin_amdgcn_update_dpp((int)y, (int)y, CTRL, 0xf, 0xf, false);
+    });
+    merge(a, b);
+}
+
+// Reduces N (a multiple of 4) statistics over the wavefront; out(k, total) runs
+// in one lane for each k.  Two steps halve the number of statistics each, by
+// exchanging halves of two of them at a time; then each row of 16 lanes holds
+// one of four, 4 a + 2 (row & 1) + (row >> 1).  (One by one, ten statistics took
+// twice the sweep of a row of 12208 samples.)
+template <int N, typename S, typename F>
+__device__ __forceinline__ void wave_reduce_all(S (&d)[N], int lane, F out)
+{
+    each<N / 2>([&](auto M) {
+        dwords(d[2 * M], d[2 * M + 1], [](uint32_t &x, uint32_t &y) {
+            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            x = r[0];
+            y = r[1];
+        });
+        merge(d[2 * M], d[2 * M + 1]);
+    });
+    each<N / 4>([&](auto A) {
+        S &t = d[4 * A];
+        dwords(t, d[4 * A + 2], [](uint32_t &x, uint32_t &y) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            x = r[0];
+            y = r[1];
+        });
+        merge(t, d[4 * A + 2]);
+        row_step<0xb1>(t);   // quad_perm [1,0,3,2]
+        row_step<0x4e>(t);   // quad_perm [2,3,0,1]
+        row_step<0x141>(t);  // row_half_mirror
+        row_step<0x140>(t);  // row_mirror
+        const int r = lane >> 4;
+        if ((lane & 15) == 0) out(4 * A + 2 * (r & 1) + (r >> 1), t);
+    });
+}
+
 // NW: the number of widths (LOOK = 4 without POW2: at least); POW2: widths are
 // 1, 2, 4, ... 2^(NW-1).  LOOK: blocks after its own that a window may end in.
 constexpr int NB = SPAN_NB;
@@ -801,17 +910,29 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
         }
     }
     // the largest centred sample (of this wavefront's)
-    long long xmax = wave_max_ll(max((long long)xhi - c, (long long)c - xlo));
+    uint32_t far = max((uint32_t)xhi - (uint32_t)c, (uint32_t)c - (uint32_t)xlo);
+    far = max(far, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)far, 0xb1, 0xf, 0xf, false));
+    far = max(far, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)far, 0x4e, 0xf, 0xf, false));
+    far = max(far, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)far, 0x141, 0xf, 0xf, false));
+    far = max(far, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)far, 0x140, 0xf, 0xf, false));
+    far = max(max((uint32_t)__builtin_amdgcn_readlane((int)far, 0), (uint32_t)__builtin_amdgcn_readlane((int)far, 16)),
+              max((uint32_t)__builtin_amdgcn_readlane((int)far, 32), (uint32_t)__builtin_amdgcn_readlane((int)far, 48)));
+    long long xmax = far;
 
     // wavefront totals: per width (max, earliest 4-output group) and sum of squares
+    constexpr int NP = (NW + 3) / 4 * 4;
+    SpanStat d[NP];
 #pragma unroll
-    for (int k = 0; k < NW; ++k) {
-        if (LOOK > 1 && k >= ws.n) continue;
-        const int u0 = jmax[k] >= 0 ? jmax[k] * kSpanBlk + 4 * lane : 0;
-        const long long key = wave_max_ll(pack_key(vmax[k], u0));
-        const double s = wave_sum_d((double)(unsigned long long)s2[k]);
-        if (lane == 0) res[wave * NW + k] = SpanRes{key, s};
+    for (int k = 0; k < NP; ++k) {
+        if (k < NW)
+            d[k] = SpanStat{vmax[k], ~(uint32_t)(jmax[k] >= 0 ? jmax[k] * kSpanBlk + 4 * lane : 0),
+                            (double)(unsigned long long)s2[k]};
+        else
+            d[k] = SpanStat{INT32_MIN, 0u, 0.0};
     }
+    wave_reduce_all(d, lane, [&](int k, const SpanStat &t) {
+        if (k < NW) res[wave * NW + k] = SpanRes{lane_key(t), t.s2};
+    });
     if (lane == 0) {
         tres[wave] = tsum;
         peaks[wave] = xmax;
@@ -954,56 +1075,6 @@ struct DecRes {
     uint32_t pad;
 };
 
-// Statistics in the form that the reduction moves between lanes.
-struct DecStat {
-    int32_t v;    // maximum
-    uint32_t nt;  // ~(its first sample)
-    double s1, s2;
-};
-
-__device__ __forceinline__ void dec_merge(DecStat &a, const DecStat &b)
-{
-    const long long ka = (long long)(((uint64_t)(uint32_t)a.v << 32) | a.nt),
-                    kb = (long long)(((uint64_t)(uint32_t)b.v << 32) | b.nt);
-    const bool up = kb > ka;
-    a.v = up ? b.v : a.v;
-    a.nt = up ? b.nt : a.nt;
-    a.s1 += b.s1;
-    a.s2 += b.s2;
-}
-
-// f(x, y) on the dwords of two statistics.
-template <typename F>
-__device__ __forceinline__ void dec_dwords(DecStat &a, DecStat &b, F f)
-{
-    auto both = [&](double &x, double &y) {
-        uint64_t p = (uint64_t)__double_as_longlong(x), q = (uint64_t)__double_as_longlong(y);
-        uint32_t pl = (uint32_t)p, ph = (uint32_t)(p >> 32), ql = (uint32_t)q, qh = (uint32_t)(q >> 32);
-        f(pl, ql);
-        f(ph, qh);
-        x = __longlong_as_double((long long)(((uint64_t)ph << 32) | pl));
-        y = __longlong_as_double((long long)(((uint64_t)qh << 32) | ql));
-    };
-    uint32_t av = (uint32_t)a.v, bv = (uint32_t)b.v;
-    f(av, bv);
-    a.v = (int32_t)av;
-    b.v = (int32_t)bv;
-    f(a.nt, b.nt);
-    both(a.s1, b.s1);
-    both(a.s2, b.s2);
-}
-
-// One step of the reduction within rows of 16 lanes.
-template <int CTRL>
-__device__ __forceinline__ void dec_step(DecStat &a)
-{
-    DecStat b = a;
-    dec_dwords(a, b, [](uint32_t &, uint32_t &y) {
-        y = (uint32_t)__builtin_amdgcn_update_dpp((int)y, (int)y, CTRL, 0xf, 0xf, false);
-    });
-    dec_merge(a, b);
-}
-
 template <bool VEC>
 __device__ __forceinline__ void dec_load(__amdgpu_buffer_rsrc_t rs, int s0, int n_out, int lane,
                                          i32x4 (&x)[kDecBlocks])
@@ -1017,19 +1088,6 @@ __device__ __forceinline__ void dec_load(__amdgpu_buffer_rsrc_t rs, int s0, int 
         else
             x[q] = span_load<false>(rs, blk, lane);
     }
-}
-
-// f(K) for K = 0 .. N - 1 as constants (a loop of this size is not always
-// unrolled, and the statistics it indexes would then live in memory).
-template <typename F, int... K>
-__device__ __forceinline__ void each_of(F f, std::integer_sequence<int, K...>)
-{
-    (f(std::integral_constant<int, K>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void each(F f)
-{
-    each_of(f, std::make_integer_sequence<int, N>{});
 }
 
 // NW: at least the number of factors, a multiple of 4.  A factor 1 comes first;
@@ -1115,37 +1173,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NW <= 12 ? 
             }
         });
     }
-    // Two steps halve the number of statistics each, by exchanging halves of two
-    // of them at a time; the third holds factor 4 a + 2 (row & 1) + (row >> 1)
-    // in each row of 16 lanes.  (Reduced one by one they took twice the sweep.)
     DecStat d[NW];
 #pragma unroll
     for (int k = 0; k < NW; ++k) d[k] = DecStat{st[k].vmax, ~st[k].tmax, st[k].s1, st[k].s2};
-    each<NW / 2>([&](auto M) {
-        dec_dwords(d[2 * M], d[2 * M + 1], [](uint32_t &x, uint32_t &y) {
-            const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-            x = r[0];
-            y = r[1];
-        });
-        dec_merge(d[2 * M], d[2 * M + 1]);
-    });
-    each<NW / 4>([&](auto A) {
-        DecStat &t = d[4 * A];
-        dec_dwords(t, d[4 * A + 2], [](uint32_t &x, uint32_t &y) {
-            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-            x = r[0];
-            y = r[1];
-        });
-        dec_merge(t, d[4 * A + 2]);
-        dec_step<0xb1>(t);   // quad_perm [1,0,3,2]
-        dec_step<0x4e>(t);   // quad_perm [2,3,0,1]
-        dec_step<0x141>(t);  // row_half_mirror
-        dec_step<0x140>(t);  // row_mirror
-        const int r = lane >> 4;
-        if ((lane & 15) == 0)
-            res[wave * NW + 4 * A + 2 * (r & 1) + (r >> 1)].st =
-                Stat{(long long)(((uint64_t)(uint32_t)t.v << 32) | t.nt), t.s1, t.s2};
-    });
+    wave_reduce_all(d, lane, [&](int k, const DecStat &t) { res[wave * NW + k].st = Stat{lane_key(t), t.s1, t.s2}; });
     if (lane == 0) total[wave] = base;
     __syncthreads();
     const int k = threadIdx.x;
