@@ -1319,9 +1319,11 @@ __global__ __launch_bounds__(1024) void snr_kernel(const int32_t *__restrict__ b
         Stat s = scratch[0];
         const int32_t vmax = (int32_t)(s.key >> 32);
         const uint32_t t0 = 0xffffffffu - (uint32_t)(s.key & 0xffffffffll);
-        uint32_t t = t0;
-        while (t < t0 + 3 && (int64_t)t + 1 < n && row[t] != vmax) ++t;
-        s.key = pack_key(vmax, t);
+        // (the three loads together)
+        const int64_t end = n - 1;
+        const int32_t v0 = row[t0], v1 = row[(int64_t)t0 + 1 < end ? (int64_t)t0 + 1 : end],
+                      v2 = row[(int64_t)t0 + 2 < end ? (int64_t)t0 + 2 : end];
+        s.key = pack_key(vmax, t0 + (v0 == vmax ? 0 : v1 == vmax ? 1 : v2 == vmax ? 2 : 3));
         finish(s, n, r, snr + (size_t)k * n_dm + i, peak ? peak + (size_t)k * n_dm + i : nullptr);
     }
 }
