@@ -670,14 +670,14 @@ void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, 
     // least of both: rounds that are full, and otherwise the longest that the
     // LDS holds.  (With T = 640 throughout, 1024 trials x 6104 samples were 320
     // work-groups, and took 1280 columns' time where two rounds of 384 do.)
-    // Rows of a batch share rounds with the other beams'.
+    // Beams of a batch of several rounds share them: the longest rows.
     const int64_t dms = (info.n_dm + kRows - 1) / kRows;
     int T = 0;
     if (!automatic && p->tile_t <= 256) {
         T = 256;
     } else if (!alone) {
         T = 640;
-        while (T > 128 && (matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes || dms * ((n_out + T - 1) / T) < 256)) T -= 128;
+        while (T > 128 && matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes) T -= 64;
     } else {
         int64_t best = 0;
         for (int t = 128; matrix_lds_bytes(t, (int)omax) <= kMaxLdsBytes; t += 8) {

@@ -115,3 +115,27 @@ def test_matrix_beams_in_one_batch(amber, torch):
         batch.launch(stream)
         torch.cuda.synchronize()
     batch.close()
+
+
+@pytest.mark.parametrize("cases", [[2, 5, 6, 13], [0, 2, 5]])
+def test_matrix_beams_with_one_tile_set(amber, torch, cases):
+    """Beams given the same explicit tiles of 32 trials are one launch, whether
+    all of them can take the matrix cores or not."""
+    print("[case] matrix batch, one tile set", cases, flush=True)
+    tiles = amber.make_tiles(dms_per_block=16, dms_per_thread=2, samples_per_thread=4, channel_unroll=8)
+    beams, refs = [], []
+    for b, c in enumerate(cases):
+        n_chan, n_dm, n_out, dm0, step, opt = CASES[c]
+        p, ref = _problem(amber, torch, n_chan, n_dm, n_out, dm0, min(step, 0.5), seed=b, **opt)
+        p["dd"] = torch.full((n_dm, n_out), -1, dtype=torch.int32, device="cuda")
+        p["snr"] = torch.zeros((1, n_dm), dtype=torch.float32, device="cuda")
+        p["peak"] = torch.zeros((1, n_dm), dtype=torch.int32, device="cuda")
+        beams.append(p)
+        refs.append(ref)
+    batch = amber.Batch(beams, (1,), tiles=[tiles] * len(beams))
+    assert batch.launches() == (1, 1)
+    batch.run()
+    torch.cuda.synchronize()
+    for p, ref in zip(beams, refs):
+        np.testing.assert_array_equal(p["dd"].cpu().numpy(), ref)
+    batch.close()
