@@ -1505,10 +1505,9 @@ amber_status launch_integrate_snr_jobs(const BoxcarPlan &p, const amber_tiles &t
     }
     if (decimate && single && longest < ((int64_t)1 << 29))
         return launch_dec_snr(p, *single, n_rows, widths, n_widths, stream);
-    // One beam with more than 8 series: passes of at most 8 series through
-    // the 8-series kernel (each pass re-reads the rows, but the statistics of
-    // 16 series per work-item need registers enough to halve the resident
-    // work-groups).
+    // One beam with more than 8 series: passes of at most 8 (narrow span
+    // kernels, as above, or for rows of 2^29 samples the chunk kernel, whose 16
+    // running statistics would halve the resident work-groups).
     if (single && n_widths > 8) {
         for (int k0 = 0; k0 < n_widths; k0 += 8) {
             BoxJob j = *single;
