@@ -157,6 +157,7 @@ struct Rem {
     int p[8];
     int S;       // remainders are below S (wave-uniform)
     int most;    // the largest shift of a trial (wave-uniform)
+    int first;   // where the first channel's window starts (wave-uniform)
 };
 
 __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
@@ -205,15 +206,8 @@ __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
     t[0] = pk_min(t[0], dpp<0xb1>(t[0]));    // quad_perm [1,0,3,2]
     const int m = ((mine >> 4) & 1) | ((mine >> 2) & 2) | (mine & 4);
     const int c2 = 16 * h + 2 * m;  // its first channel
-    v2i start = *lds<lds_v2>(k.ring + 4 * c2) + v2i{(int)(short)t[0], t[0] >> 16};
-    if (k.t0 == 0 && c2 == 0 && start.x < 0) {
-        // Two dwords that begin before the first row and end in it count as
-        // out of range as a whole: such a row's window starts where a load of
-        // two starts at the row (more remainders, in the lowest trials only).
-        const int by = (start.x + 4) & 7;
-        start.x -= by;
-        t[0] = pk_sub(t[0], by);
-    }
+    const v2i start = *lds<lds_v2>(k.ring + 4 * c2) + v2i{(int)(short)t[0], t[0] >> 16};
+    r.first = uniform(start.x);  // (lane 0 has channel 0)
     *lds<lds_w2>(k.ring + kStart + 4 * c2) = start;
     *lds<lds_i>(k.ring + kLow + 32 * h + 4 * m) = t[0];
     if (lane < 32) *lds<lds_i>(k.ring + kShift + 4 * lane) = shift;
@@ -354,16 +348,24 @@ __device__ __forceinline__ void add_chunk(const v16i &even, const v16i &odd, int
     }
 }
 
-// One pass: chunks [j0, j1) of 64 columns, remainders skip .. skip + NS - 1 in
-// r.  A chunk's even and odd columns are two products: column 2 n + phi with
-// remainder s is sample column 2 n + w, w = phi + s, so one read serves both.
+// How many columns early (0 or 4) a pass takes a group whose first channel's
+// window starts `first` samples off the buffer's begin.  A load of two dwords
+// whose first wraps out of range counts as out of range as a whole, also where
+// its second begins the row; 4 columns earlier no load is of that kind.  (Past
+// the end each dword counts by itself.)
+__device__ __forceinline__ int columns_early(int first) { return first < 0 ? (first + 4) & 4 : 0; }
+
+// One pass: chunks [j0, j1) of 64 columns, `early` columns before their place,
+// remainders skip .. skip + NS - 1 in r.  A chunk's even and odd columns are
+// two products: column 2 n + phi with remainder s is sample column 2 n + w, w =
+// phi + s, so one read serves both.
 template <int NS>
-__device__ __forceinline__ void pass(const Tile &k, const Rem &r, int c0, int skip, int j0, int j1)
+__device__ __forceinline__ void pass(const Tile &k, const Rem &r, int c0, int skip, int early, int j0, int j1)
 {
     const int lane = k.lane, h = lane >> 5, n = lane & 31;
     if (j0 >= j1) return;
     Stage st;
-    stage_begin(k, c0, skip, j0, st);
+    stage_begin(k, c0, skip - early, j0, st);
     Chunk w, w1;
     stage_load(st, w);
     stage_load(st, w1);
@@ -390,7 +392,7 @@ __device__ __forceinline__ void pass(const Tile &k, const Rem &r, int c0, int sk
         const v4i sh = *lds<lds_v4>(k.ring + kShift + 4 * (8 * g + 4 * h));
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            at[4 * g + e] = k.acc + 4 * ((8 * g + 4 * h + e) * k.pitch + 2 * n - sh[e] + kChunk * j0);
+            at[4 * g + e] = k.acc + 4 * ((8 * g + 4 * h + e) * k.pitch + 2 * n - sh[e] - early + kChunk * j0);
     }
     constexpr int kSlot = kOdd / 2;  // the ring's second slot follows the first
     stage_write(lane, st, 0, w);
@@ -568,9 +570,12 @@ void dedisperse_matrix_kernel(DedispJob single, const DedispJob *__restrict__ jo
         if (r.S > kRoughS) {
             if (part == 0) direct_group(k, c0);
         } else {
-            const int chunks = (k.cols + r.most + kChunk - 1) / kChunk;
-            const int j0 = chunks * part / parts, j1 = chunks * (part + 1) / parts;
-            for (int skip = 0; skip < r.S; skip += NS) pass<NS>(k, r, c0, skip, j0, j1);
+            const int first = (int)k.t0 + r.first;
+            for (int skip = 0; skip < r.S; skip += NS) {
+                const int early = columns_early(first + skip);
+                const int chunks = (k.cols + r.most + early + kChunk - 1) / kChunk;
+                pass<NS>(k, r, c0, skip, early, chunks * part / parts, chunks * (part + 1) / parts);
+            }
         }
         int t = 0;
         if (k.lane == 0)
