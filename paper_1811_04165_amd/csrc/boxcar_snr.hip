@@ -1318,7 +1318,9 @@ __global__ __launch_bounds__(1024) void snr_kernel(const int32_t *__restrict__ b
     if (threadIdx.x == 0) {
         Stat s = scratch[0];
         const int32_t vmax = (int32_t)(s.key >> 32);
-        const uint32_t t0 = 0xffffffffu - (uint32_t)(s.key & 0xffffffffll);
+        // a row of INT32_MIN alone: no value rose above the maximum's start, so
+        // no group was noted, and the first is the one
+        const uint32_t t0 = s.key == LLONG_MIN ? 0u : 0xffffffffu - (uint32_t)(s.key & 0xffffffffll);
         // (the three loads together)
         const int64_t end = n - 1;
         const int32_t v0 = row[t0], v1 = row[(int64_t)t0 + 1 < end ? (int64_t)t0 + 1 : end],
