@@ -16,9 +16,11 @@
 // trials x 32 channels x 32 columns for one s; the shift is the address at
 // which the 32 x 32 results are added to the work-group's sums in LDS.
 // Everything is integer and exact for every table: S is taken from the table
-// on the device, a group with a large S is cut into
-// passes of NS remainders, and a group whose channels do not move alike at
-// all is summed directly.
+// on the device, and a group with a large S is cut into passes of NS remainders.
+// Which channels make a group is free: where those that come together do not
+// move alike (a band listed in another order than by frequency), the work-group
+// sorts them by how far they move and forms groups anew.  A group that needs
+// more than kRoughS remainders even so is summed directly.
 //
 // What bounds it: per 32 channels x 64 columns a wavefront issues 2 NS products
 // (35 clocks of a SIMD each), 2 KiB of staging writes, NS + 1 reads and 16
@@ -45,6 +47,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) int32_t lds_i;
 typedef __attribute__((address_space(3))) uint32_t lds_u;
+typedef __attribute__((address_space(3))) uint16_t lds_u16;
 typedef __attribute__((address_space(3))) uint64_t lds_u64;
 typedef __attribute__((address_space(3))) const v4i lds_v4;
 typedef __attribute__((address_space(3))) v4i lds_w4;
@@ -55,7 +58,9 @@ typedef __attribute__((address_space(3))) v2i lds_w2;
 constexpr int kRows = kMatRows;  // trials per work-group: the rows of a product
 constexpr int kChunk = 64;       // columns staged at a time
 constexpr int kGroup = 32;       // channels per group: the depth of a product
-constexpr int kRoughS = 64;      // groups with more remainders are summed directly
+constexpr int kRoughS = 128;     // groups with more remainders are summed directly
+constexpr int kWindow = 2048;    // channels that are sorted together, at most
+constexpr int kBins = 1024;      // by distance (omax is below 800 where 128 columns fit)
 // LDS of a wavefront: a ring of two chunks of columns x 32 channels, 16
 // channels of one column per 16-byte line, the columns of 16 channels in a
 // plane of their own, even columns before odd ones (a group's delays pass
@@ -66,8 +71,12 @@ constexpr int kOdd = kPlane / 2;
 constexpr int kLine = 4 * kGroup + 16;  // bytes of a trial's delays, padded against bank conflicts
 constexpr int kStart = kRows * kLine, kShift = kStart + 4 * kGroup, kLow = kShift + 4 * kRows;
 constexpr int kWaveLds = 5120;  // a multiple of kOdd: ring addresses wrap within their low bits
-static_assert(kLow + 64 <= kWaveLds && kWaveLds % kOdd == 0, "tables fit");
-static_assert(2 * kPlane <= kStart, "the ring fits");
+// Sorted channels: 16 bits each, 256 in each wavefront's part between the ring
+// and the tables (the delays of sorted channels are staged without padding); in
+// wavefront 0's after the tables, a bit for each group that is set aside.
+constexpr int kOrder = 2 * kPlane, kAside = kLow + 64;
+static_assert(kAside + 32 <= kWaveLds && kWaveLds % kOdd == 0, "tables fit");
+static_assert(kOrder + 2 * kWindow / kMatWaves <= kStart && 4 * kBins <= kOrder, "the ring and the order fit");
 static_assert(kMatWaveLds == kWaveLds, "planner and kernel agree");
 
 // LDS by byte offset.
@@ -148,38 +157,59 @@ struct Tile {
     int acc, pitch;              // the sums in LDS: byte offset of row 0, dwords from row to row
     int ring;                    // LDS byte offset of the wavefront's part
     int lane;
+    // The channels at hand: count of them, in their own order, or (ORDER, in the
+    // functions below) listed in LDS, the task's from order on, as offsets from
+    // channel row0.
+    int count, order, row0;
 };
 
-// The remainders of the 32 channels from c0 on: lane l holds those of trial
+// The remainders of the 32 channels from c0 on (of those at hand): lane l holds those of trial
 // l & 31 and of the 16 channels 16 (l >> 5) + j, packed in 16-bit pairs
 // (0x7fff for channels that do not count).
 struct Rem {
     int p[8];
     int S;       // remainders are below S (wave-uniform)
     int most;    // the largest shift of a trial (wave-uniform)
-    int first;   // where the first channel's window starts (wave-uniform)
+    bool aside;  // set aside for sorting (wave-uniform; not with ORDER)
+    int first;   // where the window of the channel at the loads' base starts (wave-uniform)
 };
 
+template <int NS, bool ORDER>
 __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
 {
     const int lane = k.lane, row = min(lane & 31, k.rows - 1), h = lane >> 5;
-    const int nv = min(kGroup, k.n_chan - c0);
+    const int nv = min(kGroup, k.count - c0);
     const int pitch = 4 * k.n_chan;
+    int line = kLine;
+    // lane j's channel
+    int channel = c0 + (lane & 31);
     // The group's delays go through LDS: loaded as whole pieces of rows (8
-    // lanes of 16 bytes per trial) and read back by trial.
+    // lanes of 16 bytes per trial; the last row's may end past the table, where
+    // each dword counts by itself) and read back by trial.
+    if (!ORDER) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int i = 8 * q + (lane >> 3), piece = lane & 7;
-        const v4i x = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
-                                                  k.rd, min(i, k.rows - 1) * pitch + 4 * c0 + 16 * piece, 0, 0));
-        *lds<lds_w4>(k.ring + i * kLine + 16 * piece) = x;
+        for (int q = 0; q < 4; ++q) {
+            const int i = 8 * q + (lane >> 3), piece = lane & 7;
+            const v4i x = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+                                                      k.rd, min(i, k.rows - 1) * pitch + 4 * c0 + 16 * piece, 0, 0));
+            *lds<lds_w4>(k.ring + i * kLine + 16 * piece) = x;
+        }
+    } else {
+        line = 4 * kGroup;
+        channel = k.row0 + *lds<lds_u16>(k.order + 2 * (lane & 31));
+        int x[kRows / 2];
+#pragma unroll
+        for (int q = 0; q < kRows / 2; ++q)
+            x[q] = (int)__builtin_amdgcn_raw_buffer_load_b32(k.rd, min(2 * q + h, k.rows - 1) * pitch + 4 * channel, 0, 0);
+#pragma unroll
+        for (int q = 0; q < kRows / 2; ++q) *lds<lds_i>(k.ring + (2 * q + h) * line + 4 * (lane & 31)) = x[q];
     }
     __builtin_amdgcn_wave_barrier();
     // the shift is that of the middle channel (one outside the range that the
     // table's summary allows is clamped: sums may go wrong then, addresses may
     // not)
     const int mid = 4 * (nv >> 1);
-    const int s0 = *lds<lds_i>(k.ring + mid), si = *lds<lds_i>(k.ring + row * kLine + mid);
+    const int s0 = *lds<lds_i>(k.ring + mid), si = *lds<lds_i>(k.ring + row * line + mid);
     const int shift = min(max(si - s0, 0), k.omax) & ~1;  // even: columns are added in pairs
     r.most = uniform(wave_max(shift));
     int pair[8];  // offsets less the shift, two channels a dword
@@ -187,7 +217,7 @@ __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int o = k.ring + 64 * h + 16 * q;
-        const v4i d = *lds<lds_v4>(o + row * kLine) - *lds<lds_v4>(o);
+        const v4i d = *lds<lds_v4>(o + row * line) - *lds<lds_v4>(o);
         pair[2 * q] = pk_sub((int)__builtin_amdgcn_perm((uint32_t)d[1], (uint32_t)d[0], 0x05040100u), shift2);
         pair[2 * q + 1] = pk_sub((int)__builtin_amdgcn_perm((uint32_t)d[3], (uint32_t)d[2], 0x05040100u), shift2);
     }
@@ -209,6 +239,10 @@ __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
     const v2i start = *lds<lds_v2>(k.ring + 4 * c2) + v2i{(int)(short)t[0], t[0] >> 16};
     r.first = uniform(start.x);  // (lane 0 has channel 0)
     *lds<lds_w2>(k.ring + kStart + 4 * c2) = start;
+    if (ORDER) {
+        const uint32_t at = (uint32_t)__builtin_amdgcn_ballot_w64(channel == k.row0) & (0xffffffffu >> (kGroup - nv));
+        r.first = at ? uniform(*lds<lds_i>(k.ring + kStart + 4 * __builtin_ctz(at))) : 0;
+    }
     *lds<lds_i>(k.ring + kLow + 32 * h + 4 * m) = t[0];
     if (lane < 32) *lds<lds_i>(k.ring + kShift + 4 * lane) = shift;
     __builtin_amdgcn_wave_barrier();
@@ -216,9 +250,8 @@ __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
     const bool all = nv == kGroup && !k.keep;
     uint32_t valid = 0xffffu;
     if (!all) {
-        // lane j looks at channel c0 + j
-        const int c = c0 + (lane & 31);
-        const uint32_t ok = (uint32_t)__builtin_amdgcn_ballot_w64(c < k.n_chan && (!k.keep || k.keep[c] != 0));
+        const uint32_t ok =
+            (uint32_t)__builtin_amdgcn_ballot_w64((lane & 31) < nv && (!k.keep || k.keep[channel] != 0));
         valid = (ok >> (16 * h)) & 0xffffu;
     }
 #pragma unroll
@@ -240,6 +273,27 @@ __device__ __forceinline__ void remainders(const Tile &k, int c0, Rem &r)
         }
     }
     r.S = uniform(wave_max(max((int)(short)worst, worst >> 16))) + 1;
+    r.aside = false;
+    if (!ORDER && r.S > 2 * NS) {
+        // Sorting helps a group that goes back and forth over the tile's last
+        // trial (lanes 31 and 63), or sweeps over more than its share of the
+        // band: a group in order of frequency at the narrow end has 6.4 times
+        // its share, at most, of a band whose top is 4 times its bottom.
+        int way = 0, low = pair[0], high = pair[0];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            low = pk_min(low, pair[p]);
+            high = pk_max(high, pair[p]);
+            const int in = pair[p] >> 16, out = p < 7 ? (int)(short)pair[p < 7 ? p + 1 : 7] : in;
+            way += abs(in - (int)(short)pair[p]) + abs(out - in);
+        }
+        const int lo = min((int)(short)low, low >> 16), hi = max((int)(short)high, high >> 16);
+        const int join = abs((int)(short)__builtin_amdgcn_readlane(pair[0], 63) - (__builtin_amdgcn_readlane(pair[7], 31) >> 16));
+        const int ways = __builtin_amdgcn_readlane(way, 31) + __builtin_amdgcn_readlane(way, 63) + join;
+        const int range = max(__builtin_amdgcn_readlane(hi, 31), __builtin_amdgcn_readlane(hi, 63)) -
+                          min(__builtin_amdgcn_readlane(lo, 31), __builtin_amdgcn_readlane(lo, 63));
+        r.aside = ways > 2 * range || 2 * (r.S - 2) * k.n_chan > 13 * kGroup * k.omax;
+    }
 }
 
 // The staging of one chunk of 64 columns: lane (q, i) = (lane >> 3, lane & 7)
@@ -259,18 +313,24 @@ struct Chunk {
     v2i w[4];
 };
 
+template <bool ORDER>
 __device__ __forceinline__ void stage_begin(const Tile &k, int c0, int skip, int m, Stage &s)
 {
     const int q = k.lane >> 3, i = k.lane & 7;
-    const int64_t from = (int64_t)c0 * k.in_stride;
+    const int64_t from = (int64_t)(ORDER ? k.row0 : c0) * k.in_stride;
     const int64_t rest = k.in_bytes - from;
     s.rs = range_rsrc(k.in + from, (uint32_t)(rest < 0xfffffff0ll ? rest : 0xfffffff0ll));
     const v4i st = *lds<lds_v4>(k.ring + kStart + 16 * q);
+    v4i channel = {4 * q, 4 * q + 1, 4 * q + 2, 4 * q + 3};  // from the base
+    if (ORDER) {
+        const v2i two = *lds<lds_v2>(k.order + 8 * q);
+        channel = v4i{two.x & 0xffff, (int)((uint32_t)two.x >> 16), two.y & 0xffff, (int)((uint32_t)two.y >> 16)};
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         // columns before the first row's start wrap to offsets out of range
         // and read zeros (no sum needs them)
-        const uint32_t o = (uint32_t)(4 * q + j) * (uint32_t)k.in_stride +
+        const uint32_t o = (uint32_t)channel[j] * (uint32_t)k.in_stride +
                            (uint32_t)((int)k.t0 + st[j] + skip + kChunk * m);
         s.before[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(s.rs, o & ~3u, 0, 0);
         s.off[j] = o + 4u + 8u * (uint32_t)i;
@@ -359,13 +419,13 @@ __device__ __forceinline__ int columns_early(int first) { return first < 0 ? (fi
 // remainders skip .. skip + NS - 1 in r.  A chunk's even and odd columns are
 // two products: column 2 n + phi with remainder s is sample column 2 n + w, w =
 // phi + s, so one read serves both.
-template <int NS>
+template <int NS, bool ORDER>
 __device__ __forceinline__ void pass(const Tile &k, const Rem &r, int c0, int skip, int early, int j0, int j1)
 {
     const int lane = k.lane, h = lane >> 5, n = lane & 31;
     if (j0 >= j1) return;
     Stage st;
-    stage_begin(k, c0, skip - early, j0, st);
+    stage_begin<ORDER>(k, c0, skip - early, j0, st);
     Chunk w, w1;
     stage_load(st, w);
     stage_load(st, w1);
@@ -441,23 +501,25 @@ __device__ __forceinline__ void pass(const Tile &k, const Rem &r, int c0, int sk
 
 // A group whose channels do not move alike: every trial and channel on its
 // own, 512 columns at a time (8 per lane), four trials at once.
+template <bool ORDER>
 __device__ __forceinline__ void direct_group(const Tile &k, int c0)
 {
-    const int left = min(kGroup, k.n_chan - c0);
-    const int64_t from = (int64_t)c0 * k.in_stride;
-    const int64_t rest = k.in_bytes - from, rows = (int64_t)left * k.in_stride;
-    const __amdgpu_buffer_rsrc_t rs = range_rsrc(k.in + from, (uint32_t)(rest < rows ? rest : rows));
+    const int left = min(kGroup, k.count - c0), base = ORDER ? k.row0 : c0;
+    const int64_t from = (int64_t)base * k.in_stride;
+    const int64_t rest = k.in_bytes - from;
+    const __amdgpu_buffer_rsrc_t rs = range_rsrc(k.in + from, (uint32_t)(rest < 0xfffffff0ll ? rest : 0xfffffff0ll));
     for (int t = 0; t < k.cols; t += 512) {
         for (int i = 0; i < k.rows; i += 4) {
             uint32_t lo[4][2] = {}, hi[4][2] = {};
             int count = 0;
-            for (int c = 0; c < left; ++c) {
-                if (k.keep && k.keep[c0 + c] == 0) continue;
+            for (int j = 0; j < left; ++j) {
+                const int c = ORDER ? uniform(*lds<lds_u16>(k.order + 2 * j)) : j;  // from the base
+                if (k.keep && k.keep[base + c] == 0) continue;
                 ++count;
-                const int d0 = uniform(k.delays[c0 + c]);
+                const int d0 = uniform(k.delays[base + c]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int d = uniform(k.delays[(size_t)min(i + e, k.rows - 1) * k.n_chan + c0 + c]);
+                    const int d = uniform(k.delays[(size_t)min(i + e, k.rows - 1) * k.n_chan + base + c]);
                     const int o = d0 + min(max(d - d0, 0), k.omax);
                     const uint32_t x = (uint32_t)c * (uint32_t)k.in_stride + (uint32_t)((int)k.t0 + t + o + 8 * k.lane);
                     const auto v = __builtin_amdgcn_raw_buffer_load_b96(rs, x & ~3u, 0, 0);
@@ -484,6 +546,152 @@ __device__ __forceinline__ void direct_group(const Tile &k, int c0)
                 }
             }
         }
+    }
+}
+
+// What a work-group keeps in LDS beside the wavefronts' parts and the sums, by
+// byte offset from `next`: the next task, zapped jobs' kept channels, the
+// passes made, and the number of groups set aside (from bit 16 on) and of the
+// passes that they would have taken.
+constexpr int kKept = 4, kPasses = 8, kAsidePasses = 12;
+
+// Sorts the channels of the groups set aside among those from k.row0 on (up to
+// `window`) by how far they move over the tile's trials, where the groups formed
+// of them then take at least a fifth fewer passes; else they keep their order.
+// Leaves their list in LDS and their number in k.count.  By the whole
+// work-group, with barriers.
+__device__ __forceinline__ void regroup(Tile &k, int base, int next, int window, int ns)
+{
+    constexpr int kThreads = 64 * kMatWaves, kEach = kWindow / kThreads, kPer = kBins / 64;
+    const int tid = threadIdx.x, end = min(k.n_chan, k.row0 + window);
+    const auto slot = [&](int rank) { return lds<lds_u16>(base + (rank >> 8) * kWaveLds + kOrder + 2 * (rank & 255)); };
+    // this work-item's channels: their bins, or -1
+    int bin[kEach];
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+        const int c = k.row0 + q * kThreads + tid;
+        bin[q] = -1;
+        if (c < end && ((*lds<lds_u>(base + kAside + 4 * (c >> 10)) >> ((c >> 5) & 31)) & 1u) && (!k.keep || k.keep[c] != 0))
+            bin[q] = min(max(k.delays[(size_t)(k.rows - 1) * k.n_chan + c] - k.delays[c], 0), kBins - 1);
+    }
+    for (int b = tid; b < kBins / 4; b += kThreads) *lds<lds_w4>(base + 16 * b) = v4i{0, 0, 0, 0};
+    if (tid == 0) *lds<lds_i>(next) = kMatWaves;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kEach; ++q)
+        if (bin[q] >= 0)
+            __hip_atomic_fetch_add(lds<lds_i>(base + 4 * bin[q]), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    // the bins' first ranks, by every wavefront (wavefront 0's are kept)
+    int n[kPer], sum = 0, low = kBins, high = -1;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        n[e] = *lds<lds_i>(base + 4 * (kPer * k.lane + e));
+        low = n[e] != 0 && low == kBins ? kPer * k.lane + e : low;
+        high = n[e] != 0 ? kPer * k.lane + e : high;
+        sum += n[e];
+    }
+    int before = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(before, off, 64);
+        if (k.lane >= off) before += y;
+    }
+    const int total = __builtin_amdgcn_readlane(before, 63);
+    before -= sum;
+    // passes of sorted groups, at most: together they span the bins once
+    const int groups = (total + kGroup - 1) / kGroup;
+    const int passes = groups + (wave_max(high) + wave_max(-low) + 2 * groups) / ns;
+    // those of the window's groups as they are: the mean of the ones looked at
+    int here = 0;
+    for (int w = k.row0 >> 10; 1024 * w < end; ++w) {
+        const int from = max(k.row0 / kGroup - 32 * w, 0);
+        here += __builtin_popcount(*lds<lds_u>(base + kAside + 4 * w) >> from << from &
+                                   (end - 1024 * w >= 1024 ? 0xffffffffu : (1u << ((end - 1024 * w + kGroup - 1) / kGroup)) - 1u));
+    }
+    const int seen = *lds<lds_i>(next + kAsidePasses);
+    const bool sort = 5 * passes * (seen >> 16) < 4 * (seen & 0xffff) * here;
+    __syncthreads();
+    if (sort) {
+        if (tid < 64) {
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                *lds<lds_i>(base + 4 * (kPer * k.lane + e)) = before;
+                before += n[e];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kEach; ++q)
+            if (bin[q] >= 0)
+                *slot(__hip_atomic_fetch_add(lds<lds_i>(base + 4 * bin[q]), 1, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP)) = (uint16_t)(q * kThreads + tid);
+        k.count = total;
+    } else {
+        // whole groups one after the other
+        int rank = 0;
+        for (int c = k.row0; c < end; c += kGroup) {
+            if (!((*lds<lds_u>(base + kAside + 4 * (c >> 10)) >> ((c >> 5) & 31)) & 1u)) continue;
+            const int m = min(kGroup, end - c);
+            if (tid < m) *slot(rank + tid) = (uint16_t)(c - k.row0 + tid);
+            rank += m;
+        }
+        k.count = rank;
+    }
+    // the last group's places that no channel has
+    if (tid < (-k.count & (kGroup - 1))) *slot(k.count + tid) = 0;
+    __syncthreads();
+}
+
+// A wavefront's tasks: groups of 32 channels, each in `parts` column ranges,
+// taken by the wavefronts as they come free.  First the channels as they come;
+// groups of more than two passes that sorting may help are set aside, and their
+// channels come again after that (ORDER).
+template <int NS, bool ORDER>
+__device__ __forceinline__ void tasks(Tile &k, int base, int next, int parts, int wave)
+{
+    const auto add_to = [&](int what, int n) {
+        __hip_atomic_fetch_add(lds<lds_i>(next + what), n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    const int n_tasks = (k.count + kGroup - 1) / kGroup * parts;
+    for (int task = wave; task < n_tasks;) {
+        // what depends on the lane is worked out per task: hoisted out of this
+        // loop it would not fit the registers
+        asm volatile("" : "+v"(k.lane));
+        const int sub = task / parts, part = task - sub * parts;
+        const int c0 = sub * kGroup;
+        if (ORDER) {
+            k.order = base + (c0 >> 8) * kWaveLds + kOrder + 2 * (c0 & 255);
+        } else if (k.keep && part == 0) {
+            const int c = c0 + k.lane;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(k.lane < kGroup && c < k.n_chan && k.keep[min(c, k.n_chan - 1)] != 0);
+            if (k.lane == 0) add_to(kKept, (int)__builtin_popcountll(m));
+        }
+        Rem r;
+        remainders<NS, ORDER>(k, c0, r);
+        if (!ORDER && r.aside) {
+            if (part == 0 && k.lane == 0) {
+                __hip_atomic_fetch_or(lds<lds_u>(base + kAside + 4 * (sub >> 5)), 1u << (sub & 31), __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+                add_to(kAsidePasses, 0x10000 + min((r.S + NS - 1) / NS, 64));
+            }
+        } else {
+            if (part == 0 && k.lane == 0) add_to(kPasses, r.S > kRoughS ? 1 : (r.S + NS - 1) / NS);
+            if (r.S > kRoughS) {
+                if (part == 0) direct_group<ORDER>(k, c0);
+            } else {
+                const int first = (int)k.t0 + r.first;
+                for (int skip = 0; skip < r.S; skip += NS) {
+                    const int early = columns_early(first + skip);
+                    const int chunks = (k.cols + r.most + early + kChunk - 1) / kChunk;
+                    pass<NS, ORDER>(k, r, c0, skip, early, chunks * part / parts, chunks * (part + 1) / parts);
+                }
+            }
+        }
+        int t = 0;
+        if (k.lane == 0)
+            t = __hip_atomic_fetch_add(lds<lds_i>(next), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        task = uniform(t);
     }
 }
 
@@ -529,8 +737,7 @@ void dedisperse_matrix_kernel(DedispJob single, const DedispJob *__restrict__ jo
     k.cols = (int)(job.n_out - k.t0 < T ? job.n_out - k.t0 : T);
     const int base = (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds_raw;
     k.ring = base + wave * kWaveLds;
-    // LDS: the next task, zapped jobs' kept channels and the passes made
-    const int next = base + kMatWaves * kWaveLds, kept = next + 4, passes = next + 8;
+    const int next = base + kMatWaves * kWaveLds;
     // rows of sums, T columns and as many spare ones between two rows (and
     // before the first) as an addition may be off to either side
     const int spare = matrix_spare(job.omax), all = spare + kRows * (T + spare);
@@ -540,53 +747,30 @@ void dedisperse_matrix_kernel(DedispJob single, const DedispJob *__restrict__ jo
     for (int q = tid; q < all / 4; q += 64 * kMatWaves) *lds<lds_w4>(next + 16 + 16 * q) = v4i{0, 0, 0, 0};
     if (tid == 0) {
         *lds<lds_i>(next) = kMatWaves;
-        *lds<lds_i>(kept) = 0;
-        *lds<lds_i>(passes) = 0;
+        *lds<lds_i>(next + kKept) = 0;
+        *lds<lds_i>(next + kPasses) = 0;
+        *lds<lds_i>(next + kAsidePasses) = 0;
     }
+    if (tid < 8) *lds<lds_i>(base + kAside + 4 * tid) = 0;
     __syncthreads();
 
-    // Tasks: groups of 32 channels, each in `parts` column ranges, taken by
-    // the wavefronts as they come free.
-    const int parts = job.mat_parts;
-    const int n_tasks = (k.n_chan + kGroup - 1) / kGroup * parts;
-    for (int task = wave; task < n_tasks;) {
-        // what depends on the lane is worked out per task: hoisted out of this
-        // loop it would not fit the registers
-        asm volatile("" : "+v"(k.lane));
-        const int sub = task / parts, part = task - sub * parts;
-        const int c0 = sub * kGroup;
-        if (k.keep && part == 0) {
-            const int c = c0 + k.lane;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(k.lane < kGroup && c < k.n_chan && k.keep[min(c, k.n_chan - 1)] != 0);
-            if (k.lane == 0)
-                __hip_atomic_fetch_add(lds<lds_i>(kept), (int)__builtin_popcountll(m), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        Rem r;
-        remainders(k, c0, r);
-        if (part == 0 && k.lane == 0)
-            __hip_atomic_fetch_add(lds<lds_i>(passes), r.S > kRoughS ? 1 : (r.S + NS - 1) / NS, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (r.S > kRoughS) {
-            if (part == 0) direct_group(k, c0);
-        } else {
-            const int first = (int)k.t0 + r.first;
-            for (int skip = 0; skip < r.S; skip += NS) {
-                const int early = columns_early(first + skip);
-                const int chunks = (k.cols + r.most + early + kChunk - 1) / kChunk;
-                pass<NS>(k, r, c0, skip, early, chunks * part / parts, chunks * (part + 1) / parts);
-            }
-        }
-        int t = 0;
-        if (k.lane == 0)
-            t = __hip_atomic_fetch_add(lds<lds_i>(next), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        task = uniform(t);
-    }
+    k.count = k.n_chan;
+    k.order = k.row0 = 0;
+    tasks<NS, false>(k, base, next, job.mat_parts, wave);
     __syncthreads();
+    if (*lds<lds_i>(next + kAsidePasses) != 0) {
+        // (32-bit staging offsets from the window's first channel)
+        const int window = min(kWindow, (int)(kMaxStageSpan / k.in_stride) / kGroup * kGroup);
+        for (; k.row0 < k.n_chan; k.row0 += window) {
+            regroup(k, base, next, window, NS);
+            tasks<NS, true>(k, base, next, job.mat_parts, wave);
+            __syncthreads();
+        }
+    }
 
     // From sums of kStartSum - 128 * (sample - 128), low and high words of
     // 64-bit numbers whose low words never reach 2^32, to sums of samples.
-    const int bias = 128 * (k.keep ? *lds<lds_i>(kept) : k.n_chan) + (kStartSum / 128) * *lds<lds_i>(passes);
+    const int bias = 128 * (k.keep ? *lds<lds_i>(next + kKept) : k.n_chan) + (kStartSum / 128) * *lds<lds_i>(next + kPasses);
     const auto sum = [&](uint32_t v) { return bias - (int)(v >> 7); };
     if (job.out_u16) {  // sums known to fit 16 bits: a dword per pair
         for (int q = tid; q < k.rows * (T / 2); q += 64 * kMatWaves) {
@@ -650,6 +834,23 @@ int xcd_remap_setting()
 //
 // so: 256 channels or more, and `most` up to 18.  (`most` is an estimate from
 // the table's summary that only the speed depends on.)
+//
+// A group's columns are its tile's and omax / 2 more on average, which counts
+// where large shifts leave the LDS short rows.  512 x 8192 and 2048 x 2048, by
+// `most` times (1 + omax / 2 / longest row): 21-36 1.2-1.6, 40 (1536 channels)
+// 1.0-1.8, 33 (1024 channels) 1.0-1.2, 45 0.9-1.0, 57 0.7-0.8; so: up to 42.
+//
+// The estimate holds for channels in order of frequency at 1250-1550 MHz.  Wide
+// bands have more remainders at their bottom than it says, other orders before
+// they are sorted.  Same sizes and 64 x 2048, vector kernel's time over this
+// one's with `most` 3-4.5 / 6.5-9 / 12 / 17.9:
+//
+//   300-1200 MHz                      1.3-2.4  1.3-1.9  1.2-1.7  0.85-1.25
+//   shuffled or sub-bands in turn
+//     512 .. 1536 channels            1.4-2.6  1.2-2.4  0.6-1.8  0.8-1.0
+//     256 channels                    0.7-1.5  0.9-1.4  0.85-1.2 0.7-0.95
+//
+// (without the sorting 0.05-0.16 from 6.5 on, 0.65-1.0 below)
 void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, bool alone,
                 DedispPlan *p)
 {
@@ -666,6 +867,9 @@ void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, 
     // 1250 .. 1550 MHz is that much above its mean at the narrow end
     const double most = 2.0 + 1.37 * rate * (kRows - 1) / info.n_chan * kGroup / 2;
     if (info.n_chan < 256 || most > 18) return;
+    // the longest rows that the LDS holds
+    const int64_t longest = (kMaxLdsBytes - matrix_lds_bytes(0, (int)omax)) / (4 * kRows);
+    if (longest < 128 || most * (1.0 + 0.5 * (double)omax / (double)longest) > 42.0) return;
     // remainders per pass: more take registers (and reads) that a band with
     // fewer does not need; one pass of 12 takes less than two of 7
     const int mat = most < 5.1 ? 5 : most < 7.1 ? 7 : most < 9.1 ? 9 : 12;

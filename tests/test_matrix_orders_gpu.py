@@ -35,6 +35,10 @@ CASES = [
     (384, 64, 700, 0.0, 0.1, "shuffled"),
     (1536, 33, 515, 0.0, 0.5, "turns2"),
     (1536, 33, 515, 0.0, 2.0, "shuffled"),
+    (2304, 33, 300, 0.0, 0.25, "shuffled"),   # more channels than are sorted together
+    (387, 70, 643, 57.3, 0.35, "shuffled"),
+    (300, 40, 200, 0.0, 0.25, "blocks2"),     # a group on both sides of the sub-bands' border
+    (1536, 40, 300, 0.0, 0.5, "turns128"),    # groups that sweep over a quarter of the band
 ]
 
 
@@ -54,3 +58,41 @@ def test_any_order(n_chan, n_dm, n_out, dm0, step, order, zapped):
     dd = amber.dedisperse(torch.from_numpy(d).cuda(), info, torch.from_numpy(x).cuda(), n_in, n_out,
                           keep=None if keep is None else torch.from_numpy(keep).cuda())
     np.testing.assert_array_equal(dd.cpu().numpy(), ref)
+
+
+def test_rows_that_limit_what_is_sorted_together():
+    """Rows so far apart that 32-bit offsets reach 224 of 320 shuffled channels."""
+    import torch
+    import paper_1811_04165_amd as amber
+    n_chan, n_dm, n_out, stride = 320, 33, 300, (1 << 24) + 256
+    print("[case] matrix order, far rows", flush=True)
+    rng = np.random.default_rng(5)
+    d, info = amber.delay_table(_band(n_chan, "shuffled"), 81.92e-6, n_dm, 0.0, 0.5)
+    n_in = n_out + info.max_delay
+    x = rng.integers(0, 256, size=(n_chan, (n_in + 3) // 4 * 4), dtype=np.uint8)
+    far = torch.zeros((n_chan, stride), dtype=torch.uint8, device="cuda")
+    far[:, :x.shape[1]] = torch.from_numpy(x).cuda()
+    dd = amber.dedisperse(torch.from_numpy(d).cuda(), info, far, n_in, n_out)
+    np.testing.assert_array_equal(dd.cpu().numpy(), oracle.dedisperse(d, x, n_in, n_out))
+
+
+@pytest.mark.parametrize("zapped", [False, True])
+def test_table_of_no_dispersion_law(zapped):
+    """Channels that move as far at other trials, which no order makes alike."""
+    import torch
+    import paper_1811_04165_amd as amber
+    n_chan, n_dm, n_out = 288, 96, 1100
+    print("[case] matrix order, no law", zapped, flush=True)
+    rng = np.random.default_rng(6)
+    i = np.arange(n_dm)[:, None]
+    late = (np.arange(n_chan) % 2 == 1)[None, :]
+    d = np.where(late, 10 * np.clip(i - 16, 0, 16), 10 * np.minimum(i, 16)).astype(np.int32)
+    d += (np.arange(n_chan) % 7).astype(np.int32)[None, :]
+    _, info = amber.delay_table(_band(n_chan, "asc"), 81.92e-6, n_dm, 0.0, 0.0)
+    info.max_delay, info.max_step = int(d.max()), 10
+    n_in = n_out + info.max_delay
+    x = rng.integers(0, 256, size=(n_chan, (n_in + 3) // 4 * 4), dtype=np.uint8)
+    keep = (rng.random(n_chan) > 0.15).astype(np.uint8) if zapped else np.ones(n_chan, dtype=np.uint8)
+    dd = amber.dedisperse(torch.from_numpy(d).cuda(), info, torch.from_numpy(x).cuda(), n_in, n_out,
+                          keep=torch.from_numpy(keep).cuda() if zapped else None)
+    np.testing.assert_array_equal(dd.cpu().numpy(), oracle.dedisperse_masked(d, x, n_in, n_out, keep))
