@@ -708,15 +708,6 @@ void dedisperse_matrix_kernel(DedispJob single, const DedispJob *__restrict__ jo
         job = jobs[j];
         block -= job.block_start;
     }
-    if (job.groups > 1) {  // independent problems of one shape, back to back in the grid
-        const int gi = block / job.group_blocks;
-        block -= gi * job.group_blocks;
-        job.delays += gi * job.group_delays;
-        job.in += gi * job.group_in;
-        job.in_bytes -= gi * job.group_in;
-        job.dd = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(job.dd) + gi * job.group_out);
-        if (job.keep) job.keep += gi * job.group_keep;
-    }
     int tx, ty;
     tile_of_block(block, job.tiles_t, job.tiles_dm, remap, tx, ty);
     const int tid = threadIdx.x, wave = uniform(tid >> 6);
@@ -772,22 +763,6 @@ void dedisperse_matrix_kernel(DedispJob single, const DedispJob *__restrict__ jo
     // 64-bit numbers whose low words never reach 2^32, to sums of samples.
     const int bias = 128 * (k.keep ? *lds<lds_i>(next + kKept) : k.n_chan) + (kStartSum / 128) * *lds<lds_i>(next + kPasses);
     const auto sum = [&](uint32_t v) { return bias - (int)(v >> 7); };
-    if (job.out_u16) {  // sums known to fit 16 bits: a dword per pair
-        for (int q = tid; q < k.rows * (T / 2); q += 64 * kMatWaves) {
-            const int row = q / (T / 2), t = 2 * (q - row * (T / 2));
-            if (t >= k.cols) continue;
-            const lds_u *v = lds<lds_u>(k.acc + 4 * (row * k.pitch + t));
-            const int a = sum(v[0]), b = sum(v[1]);
-            uint16_t *out = reinterpret_cast<uint16_t *>(job.dd) + (size_t)(i0 + row) * job.dd_stride + k.t0 + t;
-            if (job.store_vec && t + 2 <= k.cols) {
-                *reinterpret_cast<uint32_t *>(out) = (uint32_t)a | ((uint32_t)b << 16);
-            } else {
-                out[0] = (uint16_t)a;
-                if (t + 1 < k.cols) out[1] = (uint16_t)b;
-            }
-        }
-        return;
-    }
     if (job.dd_stride % 4 == 0 && ((uintptr_t)job.dd & 15) == 0) {
         for (int q = tid; q < k.rows * (T / 4); q += 64 * kMatWaves) {
             const int row = q / (T / 4), t = 4 * (q - row * (T / 4));
