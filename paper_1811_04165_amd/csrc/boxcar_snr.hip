@@ -377,7 +377,7 @@ __global__ __launch_bounds__(MAXT) void integrate_snr_kernel(BoxJob single, cons
 //    width w, at u + w: box' = Q[u + w] - Q[u] is the width-w boxcar minus
 //    w c, exact in uint32 arithmetic because its true value fits int32;
 //  - per width it keeps the running maximum (3-input maxima of its 4 values),
-//    the block where that maximum last rose, and the sum of squares in int64
+//    the block where that maximum last rose, and the sum of squares in 64 bits
 //    (one 32 x 32 + 64-bit multiply-add per value).
 // A boxcar fits int32 while width x max |centred sample| does, a lane's sum of
 // squares 64 bits while its square times the values per lane does, and a
@@ -555,13 +555,13 @@ __device__ __forceinline__ int span_width(const WidthSet &ws, int k)
 // false) or valid below n_valid (TAIL true).
 template <bool TAIL>
 __device__ __forceinline__ void span_acc(const int32_t (&x)[4], int t0, int n_valid, int32_t &vmax, int32_t &jmax,
-                                         long long &s2, int32_t j)
+                                         unsigned long long &s2, int32_t j)
 {
     int32_t m;
     if (!TAIL) {
         m = max3i(max3i(vmax, x[0], x[1]), x[2], x[3]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s2 += (long long)x[e] * (long long)x[e];
+        for (int e = 0; e < 4; ++e) s2 += (unsigned long long)((long long)x[e] * (long long)x[e]);
     } else {
         m = vmax;
 #pragma unroll
@@ -569,7 +569,7 @@ __device__ __forceinline__ void span_acc(const int32_t (&x)[4], int t0, int n_va
             const bool ok = t0 + e < n_valid;
             m = ok ? max(m, x[e]) : m;
             const int32_t v = ok ? x[e] : 0;
-            s2 += (long long)v * (long long)v;
+            s2 += (unsigned long long)((long long)v * (long long)v);
         }
     }
     jmax = m != vmax ? j : jmax;
@@ -580,7 +580,7 @@ __device__ __forceinline__ void span_acc(const int32_t (&x)[4], int t0, int n_va
 // block's are in the ring).
 template <int NW, bool POW2, bool TAIL, int LOOK>
 __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane, const WidthSet &ws, int n_out,
-                                           int32_t (&vmax)[NW], int32_t (&jmax)[NW], long long (&s2)[NW])
+                                           int32_t (&vmax)[NW], int32_t (&jmax)[NW], unsigned long long (&s2)[NW])
 {
     const int b = (j & (LOOK == 1 ? 1 : 7)) * kSpanBlk + 4 * lane;
     const int t0 = j * kSpanBlk + 4 * lane;
@@ -839,7 +839,7 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
     const int n_min = n_out - maxw + 1;  // outputs below it are valid for every width
 
     int32_t vmax[NW], jmax[NW];
-    long long s2[NW];
+    unsigned long long s2[NW];
 #pragma unroll
     for (int k = 0; k < NW; ++k) {
         vmax[k] = INT32_MIN;
@@ -926,7 +926,7 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
     for (int k = 0; k < NP; ++k) {
         if (k < NW)
             d[k] = SpanStat{vmax[k], ~(uint32_t)(jmax[k] >= 0 ? jmax[k] * kSpanBlk + 4 * lane : 0),
-                            (double)(unsigned long long)s2[k]};
+                            (double)s2[k]};
         else
             d[k] = SpanStat{INT32_MIN, 0u, 0.0};
     }
