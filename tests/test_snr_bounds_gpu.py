@@ -21,11 +21,11 @@ def _check(dd, widths, threads):
 
 
 def test_lane_sums_between_63_and_64_bits():
-    """Rows centred on a first sample of 0: one wavefront's lane adds 160
-    squares of 1024 * 3e5, 1.5e19, below the bound of 1.8e19 and above 2^63."""
+    """Rows centred on a first sample of 0: one wavefront's lane adds 168
+    squares of 512 * 6e5, 1.6e19, below the bound of 1.8e19 and above 2^63."""
     print("[case] lane sums past 63 bits", flush=True)
     rng = np.random.default_rng(1)
-    dd = rng.integers(298000, 302000, size=(3, 256 * 44)).astype(np.int32)
+    dd = rng.integers(598000, 602000, size=(3, 256 * 44)).astype(np.int32)
     dd[:, 0] = 0
-    assert 160 * (1024 * 298000) ** 2 > 2 ** 63 and 176 * (1024 * 302000) ** 2 < 1.8e19
-    _check(dd, (1024,), 64)
+    assert 164 * (512 * 598000) ** 2 > 2 ** 63 and 176 * (512 * 602000) ** 2 < 1.8e19
+    _check(dd, (512,), 64)
