@@ -382,9 +382,9 @@ __global__ __launch_bounds__(MAXT) void integrate_snr_kernel(BoxJob single, cons
 // A boxcar fits int32 while width x max |centred sample| does, a lane's sum of
 // squares 64 bits while its square times the values per lane does, and a
 // block's total int32 while max |centred sample| < 2^23; each wavefront tracks
-// its largest centred sample, and a width that breaks a bound has its
-// statistics recomputed after the sweep (no dedispersed uint8 data of fewer
-// than 32 896 channels comes near it at 64 samples).  The sum of box' over the
+// its largest centred sample, and a width that breaks a bound (a first sample
+// far from the others, a wide boxcar and a long row together) is swept again in
+// FP64 after the first sweep (span_again).  The sum of box' over the
 // row needs no per-output work: it is w T minus head and tail terms, with T the
 // centred row's sum.  After the sweep: wavefront reductions, one barrier, then
 // per width one wavefront finds the first index of the maximum (its 4 candidate
@@ -552,8 +552,11 @@ __device__ __forceinline__ int span_width(const WidthSet &ws, int k)
 }
 
 // One block of one width: the lane's 4 boxcar values x, all valid (TAIL
-// false) or valid below n_valid (TAIL true).
-template <bool TAIL>
+// false) or valid below n_valid (TAIL true).  CHAIN: one multiply-add after the
+// other; the compiler else adds the four products up first in some kernels, an
+// addition more (widths 1 .. 1024 5 % slower; widths of any remainder, whose
+// values come later, 4-10 % faster so).
+template <bool TAIL, bool CHAIN>
 __device__ __forceinline__ void span_acc(const int32_t (&x)[4], int t0, int n_valid, int32_t &vmax, int32_t &jmax,
                                          unsigned long long &s2, int32_t j)
 {
@@ -561,7 +564,10 @@ __device__ __forceinline__ void span_acc(const int32_t (&x)[4], int t0, int n_va
     if (!TAIL) {
         m = max3i(max3i(vmax, x[0], x[1]), x[2], x[3]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s2 += (unsigned long long)((long long)x[e] * (long long)x[e]);
+        for (int e = 0; e < 4; ++e) {
+            s2 += (unsigned long long)((long long)x[e] * (long long)x[e]);
+            if (CHAIN) asm("" : "+v"(s2));
+        }
     } else {
         m = vmax;
 #pragma unroll
@@ -608,7 +614,7 @@ __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane
                 x[0] = (int32_t)(E.x - A.x); x[1] = (int32_t)(E.y - A.y);
                 x[2] = (int32_t)(E.z - A.z); x[3] = (int32_t)(E.w - A.w);
             }
-            span_acc<TAIL>(x, t0, n_out - (1 << k) + 1, vmax[k], jmax[k], s2[k], j);
+            span_acc<TAIL, true>(x, t0, n_out - (1 << k) + 1, vmax[k], jmax[k], s2[k], j);
         }
         return;
     }
@@ -639,7 +645,7 @@ __device__ __forceinline__ void span_block(const uint32_t *ring, int j, int lane
             case 2: span_box<2>(g, A, x); break;
             default: span_box<3>(g, A, x); break;
             }
-            span_acc<TAIL>(x, t0, n_out - w + 1, vmax[k], jmax[k], s2[k], j);
+            span_acc<TAIL, false>(x, t0, n_out - w + 1, vmax[k], jmax[k], s2[k], j);
         }
     }
 }
@@ -799,12 +805,75 @@ __device__ __forceinline__ void wave_reduce_all(S (&d)[N], int lane, F out)
     });
 }
 
+// The statistics of the widths in `again` (bits) over a wavefront's blocks
+// [jb, je) once more, of the samples as they are (where a boxcar of them fits
+// int32) and in FP64 about the boxcar of c: up to 4 widths per sweep.  Leaves in
+// res the maximum with its first index and the sum of squares, in s1 the sum.
+// 1024 rows x 200000 samples that begin with 0, us: widths 1 .. 1024 2720 ->
+// 590, width 1024 alone 2940 -> 360 (before, one wavefront slid each such window
+// along its row, uncoalesced; LDS chunks in FP64 take 1900 and 490).
+template <int NW, bool POW2, bool VEC, int LOOK>
+__device__ __forceinline__ void span_again(uint32_t again, uint32_t *ring, const int32_t *__restrict__ row,
+                                           __amdgpu_buffer_rsrc_t rs, int n_out, int32_t c, int jb, int je, int lane,
+                                           const WidthSet &ws, SpanRes *res, double *s1)
+{
+    constexpr int kTogether = 2;
+    while (again) {
+        int width[kTogether], at[kTogether], n = 0;
+        Run st[kTogether];
+#pragma unroll
+        for (int q = 0; q < kTogether; ++q) {
+            run_init(st[q]);
+            width[q] = at[q] = 0;
+            if (!again) continue;
+            at[q] = __builtin_ctz(again);
+            width[q] = POW2 ? 1 << at[q] : ws.w[at[q]];
+            again &= again - 1;
+            ++n;
+        }
+        uint32_t base = 0;
+        int32_t lo = 0, hi = 0;
+        auto put = [&](int blk) {
+            base += span_put<VEC, LOOK>(ring, blk, span_load<VEC>(rs, blk, lane), row, n_out, 0, base, lane, lo, hi);
+        };
+        if (jb < je)
+            for (int m = 0; m < LOOK; ++m) put(jb + m);
+#pragma unroll 1
+        for (int j = jb; j < je; ++j) {
+            put(j + LOOK);
+            wave_sync_lds();
+            const int b = (j & (LOOK == 1 ? 1 : 7)) * kSpanBlk + 4 * lane, t0 = j * kSpanBlk + 4 * lane;
+#pragma unroll
+            for (int q = 0; q < kTogether; ++q) {
+                if (q >= n) continue;
+                const double r = (double)c * (double)width[q];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int to = b + e + width[q];
+                    const uint32_t x = ring[LOOK == 1 ? to : to & (kSpanWideRing - 1)] - ring[b + e];
+                    if (t0 + e <= n_out - width[q]) run_add(st[q], (int32_t)x, (uint32_t)(t0 + e), r);
+                }
+            }
+            wave_sync_lds();
+        }
+#pragma unroll
+        for (int q = 0; q < kTogether; ++q) {
+            if (q >= n) continue;
+            const Stat t = wave_reduce(run_stat(st[q]));
+            if (lane == 0) {
+                res[at[q]] = SpanRes{t.key, t.s2};
+                s1[at[q]] = t.s1;
+            }
+        }
+    }
+}
+
 // NW: the number of widths (LOOK = 4 without POW2: at least); POW2: widths are
 // 1, 2, 4, ... 2^(NW-1).  LOOK: blocks after its own that a window may end in.
 constexpr int NB = SPAN_NB;
 template <int NW, bool POW2, bool VEC, int LOOK>
-__global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob single, const BoxJob *__restrict__ jobs, int n_jobs,
-                                                        WidthSet ws)
+__global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) __attribute__((amdgpu_waves_per_eu(LOOK == 1 || NW == 11 ? 4 : 2)))
+void span_snr_kernel(BoxJob single, const BoxJob *__restrict__ jobs, int n_jobs, WidthSet ws)
 {
     extern __shared__ uint4 lds4[];
     // the wavefront index is uniform: keep it (and the span bounds, the block
@@ -815,6 +884,7 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
     SpanRes *res = reinterpret_cast<SpanRes *>(reinterpret_cast<uint32_t *>(lds4) + W * kRing);
     long long *tres = reinterpret_cast<long long *>(res + W * NW);
     long long *peaks = tres + W;  // per wavefront: its largest centred sample
+    double *sums = reinterpret_cast<double *>(peaks + W);  // per wavefront and width, of those swept again
 
     int i = blockIdx.x;
     BoxJob job = single;
@@ -943,11 +1013,35 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
         xmax = max(xmax, peaks[v]);
         T += tres[v];
     }
+    const int blocks = (nb + W - 1) / W;
+    // Exact: a block's total (256 centred samples) and a boxcar fit int32, and a
+    // lane's sum of squares (at most 4 values a block) 64 bits.
+    auto exact = [&](int w) {
+        const double bound = (double)w * (double)xmax;
+        return xmax < (1 << 23) && bound < 2147483647.0 && bound * bound * (4.0 * (double)blocks) < 1.8e19;
+    };
+    uint32_t again = 0, slow = 0;  // widths to sweep again, and those that no sweep holds
+    if (__builtin_expect(!exact(maxw), 0)) {
+#pragma unroll 1
+        for (int k = 0; k < (LOOK == 1 ? NW : ws.n); ++k) {
+            const int w = span_width<POW2>(ws, k);
+            if (exact(w)) continue;
+            // (where boxcars of the samples themselves fit int32)
+            if ((double)w * ((double)xmax + fabs((double)c)) < 2147483648.0)
+                again |= 1u << k;
+            else
+                slow |= 1u << k;
+        }
+        again = (uint32_t)__builtin_amdgcn_readfirstlane((int)again);
+        slow = (uint32_t)__builtin_amdgcn_readfirstlane((int)slow);
+        span_again<NW, POW2, VEC, LOOK>(again, ring, row, rs, n_out, c, jb, je, lane, ws, res + wave * NW,
+                                        sums + wave * NW);
+        __syncthreads();
+    }
     // this wavefront's widths k = wave, wave + W, ..: totals over the
     // wavefronts (in a fixed order), then the loads that find the first index
     // of each maximum among outputs u0 .. u0 + 3 (the samples that enter and
     // leave from one to the next), all issued before any is used
-    const int blocks = (nb + W - 1) / W;
     long long key[NW];
     double s2t[NW];
     int32_t edge[NW];
@@ -973,10 +1067,11 @@ __global__ __launch_bounds__(LOOK == 1 ? 1024 : 512) void span_snr_kernel(BoxJob
         double vm = (double)(int32_t)(key[k] >> 32);
         int tstar = (int)(0xffffffffu - (uint32_t)(key[k] & 0xffffffffll));
         double s1, s = s2t[k];
-        // Exact: a block's total (256 centred samples) and a boxcar fit int32,
-        // and a lane's sum of squares (at most 4 values a block) 64 bits.
-        const double bound = (double)w * (double)xmax;
-        if (xmax < (1 << 23) && bound < 2147483647.0 && bound * bound * (4.0 * (double)blocks) < 1.8e19) {
+        if ((again >> k) & 1u) {
+            s1 = 0.0;
+            for (int v = 0; v < W; ++v) s1 += sums[v * NW + k];
+            vm -= (double)w * (double)c;
+        } else if (!((slow >> k) & 1u)) {
             // the boxcar sum's weights below w: its head's and tail's samples
             double corr = 0.0;
             auto ends = [&](int m, int32_t xh, int32_t xt) {
@@ -1415,7 +1510,7 @@ amber_status launch_span_snr(const BoxcarPlan &p, const BoxJob *single, const Bo
     const int nw = !wide || pow2 ? n_widths : (n_widths + 3) / 4 * 4;
     const int threads = wide && p.threads > 512 ? 512 : p.threads;
     const int W = threads / kWave;
-    const size_t lds = (size_t)W * (wide ? kSpanWideRing : kSpanRing) * 4 + (size_t)W * nw * sizeof(SpanRes) +
+    const size_t lds = (size_t)W * (wide ? kSpanWideRing : kSpanRing) * 4 + (size_t)W * nw * (sizeof(SpanRes) + sizeof(double)) +
                        2 * (size_t)W * sizeof(long long);
     const BoxJob one = single ? *single : BoxJob{};
     const dim3 grid((unsigned)n_rows), block(threads);
