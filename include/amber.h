@@ -119,10 +119,12 @@ typedef struct {
  * Brute-force dedispersion of 256 or more channels whose neighbours move
  * nearly alike runs on the matrix cores, 32 DMs per work-group: always with
  * automatic tiles, and also with tiles of 32 DMs (dms_per_block *
- * dms_per_thread) that stage through LDS (in a batch where that holds for all
- * beams given the same tiles, which stay one launch).  Such tiles must be valid as ever;
- * of them threads_per_dm * samples_per_thread then chooses between rows of 256
- * samples (up to 256) and the longest that fit.  Results are the same. */
+ * dms_per_thread) that stage through LDS (in a batch, and among chunks that the
+ * streaming service runs together, where that holds for all beams given the
+ * same tiles, which stay one launch).  Such tiles must be valid as ever; of them
+ * threads_per_dm * samples_per_thread then chooses between rows of 256 samples
+ * (up to 256) and rows as long as full rounds of work-groups want.  Results are
+ * the same. */
 typedef struct {
     int32_t threads_per_dm;
     int32_t samples_per_thread;

@@ -400,7 +400,7 @@ amber_status dedisperse_common(const int32_t *d_delays, const amber_delay_info *
     if (n_out == 0) return AMBER_OK;
     // (tiles whose zeroed region for zapped channels does not fit are refused below)
     if (!d_keep || plan.lds_bytes + mask_lds_bytes(plan) <= kMaxLdsBytes)
-        use_matrix(*info, in_stride, n_out, tiles == nullptr, true, &plan);
+        use_matrix(*info, in_stride, n_out, tiles == nullptr, &plan);
     if (plan.direct) {
         DedispJob j = make_dedisp_job(plan, d_delays, info->n_dm, info->n_chan, d_in, in_stride, d_dd, dd_stride,
                                       n_out);

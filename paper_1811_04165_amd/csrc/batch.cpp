@@ -24,53 +24,6 @@ amber_status check_beam(const amber_beam &b, int k, const int32_t *widths, int n
     return AMBER_OK;
 }
 
-// Matrix-core plans where they are the faster ones.  Beams with the same
-// explicit tiles stay one launch: all of them take the matrix cores, in one
-// form (the most remainders per pass and the shortest rows of theirs), or none.
-void use_matrix_in_batch(const amber_beam *beams, int n, const std::vector<amber_tiles> &ts, bool automatic,
-                         std::vector<DedispPlan> *dps)
-{
-    // work-groups of 32 trials x 640 samples: with four rounds of 256 or more,
-    // a beam's row length does not have to fill rounds by itself
-    int64_t blocks = 0;
-    for (int k = 0; k < n; ++k) blocks += ((beams[k].info.n_dm + 31) / 32) * ((beams[k].n_out + 639) / 640);
-    const bool alone = blocks < 1024;
-    std::vector<DedispPlan> m = *dps;
-    for (int k = 0; k < n; ++k)
-        use_matrix(beams[k].info, beams[k].in_stride, beams[k].n_out, automatic, automatic && alone, &m[k]);
-    if (automatic) {
-        *dps = m;
-        return;
-    }
-    auto same = [&](int a, int b) {
-        const amber_tiles &x = ts[a], &y = ts[b];
-        return x.threads_per_dm == y.threads_per_dm && x.samples_per_thread == y.samples_per_thread &&
-               x.dms_per_block == y.dms_per_block && x.channel_unroll == y.channel_unroll &&
-               x.dms_per_thread == y.dms_per_thread && x.direct_reads == y.direct_reads;
-    };
-    std::vector<char> done(n, 0);
-    for (int k = 0; k < n; ++k) {
-        if (done[k]) continue;
-        bool all = true;
-        int mat = 0, tile_t = m[k].tile_t;
-        for (int j = k; j < n; ++j) {
-            if (!same(k, j)) continue;
-            all = all && m[j].mat != 0;
-            mat = std::max(mat, m[j].mat);
-            tile_t = std::min(tile_t, m[j].tile_t);
-        }
-        for (int j = k; j < n; ++j) {
-            if (!same(k, j)) continue;
-            done[j] = 1;
-            if (!all) continue;
-            (*dps)[j] = m[j];
-            (*dps)[j].mat = mat;
-            (*dps)[j].tile_t = tile_t;
-            (*dps)[j].lds_bytes = matrix_lds_bytes(tile_t, m[j].omax);
-        }
-    }
-}
-
 }  // namespace
 }  // namespace amber
 
@@ -139,7 +92,10 @@ amber_status amber_batch_create(const amber_beam *beams, int32_t n_beams, const 
             return s;
         }
     }
-    use_matrix_in_batch(beams, n_beams, ts, tiles == nullptr, &dps);
+    std::vector<MatrixUse> uses;
+    for (int k = 0; k < n_beams; ++k)
+        uses.push_back({&beams[k].info, beams[k].in_stride, beams[k].n_out, tiles ? &ts[k] : nullptr});
+    use_matrix_together(uses, &dps);
     // group beams by identical launch shapes
     for (int k = 0; k < n_beams; ++k) {
         const amber_beam &bm = beams[k];

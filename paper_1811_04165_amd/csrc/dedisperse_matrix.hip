@@ -37,6 +37,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <type_traits>
+#include <vector>
 
 namespace amber {
 namespace {
@@ -788,6 +789,40 @@ void dedisperse_matrix_kernel(DedispJob single, const DedispJob *__restrict__ jo
 
 }  // namespace
 
+namespace {
+
+struct Sizes {
+    int64_t n_dm, n_out;
+};
+
+// Row length of problems that run in one launch.  A work-group fills a CU, so a
+// launch takes rounds of 256; in each it takes the time of about T + omax / 2
+// columns plus its delays', passes' and last step's, about 400 columns' more.
+// The length with the least of both: rounds that are full, and otherwise the
+// longest that the LDS holds.  (With T = 640 throughout, 1024 trials x 6104
+// samples were 320 work-groups, and took 1280 columns' time where two rounds of
+// 384 do.)  0: none fits.
+int row_length(const Sizes *problems, size_t n, int omax)
+{
+    int64_t longest = 0, best = 0;
+    for (size_t k = 0; k < n; ++k) longest = std::max(longest, problems[k].n_out);
+    int T = 0;
+    for (int t = 128; matrix_lds_bytes(t, omax) <= kMaxLdsBytes; t += 8) {
+        int64_t blocks = 0;
+        for (size_t k = 0; k < n; ++k)
+            blocks += (problems[k].n_dm + kRows - 1) / kRows * ((problems[k].n_out + t - 1) / t);
+        const int64_t cost = (blocks + 255) / 256 * (t + omax / 2 + 400);
+        if (T == 0 || cost < best) {
+            best = cost;
+            T = t;
+        }
+        if (t >= longest) break;
+    }
+    return T;
+}
+
+}  // namespace
+
 int xcd_remap_setting()
 {
     const char *e = getenv("AMBER_XCD_REMAP");
@@ -826,8 +861,7 @@ int xcd_remap_setting()
 //     256 channels                    0.7-1.5  0.9-1.4  0.85-1.2 0.7-0.95
 //
 // (without the sorting 0.05-0.16 from 6.5 on, 0.65-1.0 below)
-void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, bool alone,
-                DedispPlan *p)
+void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, DedispPlan *p)
 {
     if (p->in_u16 || p->direct || n_out < 1) return;
     if (!automatic && p->dpb * p->dpt != kRows) return;  // explicit tiles choose the trials per work-group
@@ -848,32 +882,9 @@ void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, 
     // remainders per pass: more take registers (and reads) that a band with
     // fewer does not need; one pass of 12 takes less than two of 7
     const int mat = most < 5.1 ? 5 : most < 7.1 ? 7 : most < 9.1 ? 9 : 12;
-    // Row length.  A work-group fills a CU, so a launch takes rounds of 256; in
-    // each it takes the time of about T + omax / 2 columns plus its delays',
-    // passes' and last step's, about 400 columns' more.  The length with the
-    // least of both: rounds that are full, and otherwise the longest that the
-    // LDS holds.  (With T = 640 throughout, 1024 trials x 6104 samples were 320
-    // work-groups, and took 1280 columns' time where two rounds of 384 do.)
-    // Beams of a batch of several rounds share them: the longest rows.
-    const int64_t dms = (info.n_dm + kRows - 1) / kRows;
-    int T = 0;
-    if (!automatic && p->tile_t <= 256) {
-        T = 256;
-    } else if (!alone) {
-        T = 640;
-        while (T > 128 && matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes) T -= 64;
-    } else {
-        int64_t best = 0;
-        for (int t = 128; matrix_lds_bytes(t, (int)omax) <= kMaxLdsBytes; t += 8) {
-            const int64_t rounds = (dms * ((n_out + t - 1) / t) + 255) / 256;
-            const int64_t cost = rounds * (t + omax / 2 + 400);
-            if (T == 0 || cost < best) {
-                best = cost;
-                T = t;
-            }
-            if (t >= n_out) break;
-        }
-    }
+    // explicit tiles of up to 256 samples choose that
+    const Sizes size{info.n_dm, n_out};
+    const int T = !automatic && p->tile_t <= 256 ? 256 : row_length(&size, 1, (int)omax);
     if (T == 0 || matrix_lds_bytes(T, (int)omax) > kMaxLdsBytes) return;
     p->mat = mat;
     p->omax = (int)omax;
@@ -884,6 +895,53 @@ void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, 
     // few groups: column ranges of each, so that every wavefront has two tasks
     const int groups = (info.n_chan + kGroup - 1) / kGroup;
     p->mat_parts = std::max(1, std::min(4, 2 * kMatWaves / groups));
+}
+
+// Beams of one launch set.  Those with the same explicit tiles stay one launch:
+// all of them take the matrix cores, or none.  Those with automatic tiles run in
+// one launch for each form of the kernel (remainders per pass).  With a row
+// length and a launch for each beam, 8 beams of 512 channels x 256 trials x 3000
+// to 7900 samples took 168 us where one launch takes 101, 16 of 256 x 64 x 2000
+// to 7000 90 and 53.
+void use_matrix_together(const std::vector<MatrixUse> &beams, std::vector<DedispPlan> *plans)
+{
+    const size_t n = beams.size();
+    std::vector<DedispPlan> m = *plans;
+    for (size_t k = 0; k < n; ++k)
+        use_matrix(*beams[k].info, beams[k].in_stride, beams[k].n_out, beams[k].tiles == nullptr, &m[k]);
+    const auto same = [&](size_t a, size_t b) {
+        const amber_tiles *x = beams[a].tiles, *y = beams[b].tiles;
+        if (!x || !y) return !x && !y && m[a].mat == m[b].mat;
+        return x->threads_per_dm == y->threads_per_dm && x->samples_per_thread == y->samples_per_thread &&
+               x->dms_per_block == y->dms_per_block && x->channel_unroll == y->channel_unroll &&
+               x->dms_per_thread == y->dms_per_thread && x->direct_reads == y->direct_reads;
+    };
+    std::vector<char> done(n, 0);
+    for (size_t k = 0; k < n; ++k) {
+        if (done[k]) continue;
+        bool all = true;
+        int mat = 0, omax = 0;
+        std::vector<size_t> set;
+        std::vector<Sizes> sizes;
+        for (size_t j = k; j < n; ++j) {
+            if (done[j] || !same(k, j)) continue;
+            done[j] = 1;
+            set.push_back(j);
+            sizes.push_back({beams[j].info->n_dm, beams[j].n_out});
+            all = all && m[j].mat != 0;
+            mat = std::max(mat, m[j].mat);
+            omax = std::max(omax, m[j].omax);
+        }
+        if (!all) continue;
+        const bool short_rows = beams[k].tiles && (*plans)[k].tile_t <= 256;
+        const int T = set.size() == 1 ? m[k].tile_t : short_rows ? 256 : row_length(sizes.data(), sizes.size(), omax);
+        for (size_t j : set) {
+            (*plans)[j] = m[j];
+            (*plans)[j].mat = mat;
+            (*plans)[j].tile_t = T;
+            (*plans)[j].lds_bytes = matrix_lds_bytes(T, m[j].omax);
+        }
+    }
 }
 
 amber_status launch_dedisperse_matrix_jobs(const DedispPlan &p, const DedispJob *single, const DedispJob *d_jobs,

@@ -71,10 +71,16 @@ constexpr int64_t matrix_lds_bytes(int tile_t, int omax)
     return kMatWaves * kMatWaveLds + 16 + 4ll * (matrix_spare(omax) + kMatRows * (tile_t + matrix_spare(omax)));
 }
 // Turns a staged uint8 plan into a matrix-core plan where that is the faster
-// kernel (see the rule there); automatic: the tiles are the library's choice;
-// alone: the problem has a launch of its own.
-void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, bool alone,
-                DedispPlan *p);
+// kernel (see the rule there); automatic: the tiles are the library's choice.
+void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, bool automatic, DedispPlan *p);
+// The same for beams that run together, in as few launches as there are forms
+// of the kernel and explicit tile sets among them.
+struct MatrixUse {
+    const amber_delay_info *info;
+    int64_t in_stride, n_out;
+    const amber_tiles *tiles;  // NULL: the library's choice
+};
+void use_matrix_together(const std::vector<MatrixUse> &beams, std::vector<DedispPlan> *plans);
 // 1 unless AMBER_XCD_REMAP=0: neighbouring tiles share an XCD's L2.
 int xcd_remap_setting();
 // LDS a launch with keep flags adds: the zeroed region zapped channels read

@@ -132,6 +132,7 @@ struct SBeam {
     std::vector<int32_t> widths;
     int maxw = 0;
     amber_tiles tiles{};
+    bool automatic = true;        // the tiles are the library's choice
     DedispPlan dp{};
     BoxcarPlan bp{};
     int64_t dd_stride = 0;        // int32 per dedispersed row of a chunk block
@@ -265,6 +266,17 @@ void release_active(amber_server *s, Active &a)
 amber_status enqueue(amber_server *s, Flight &f, hipStream_t stream)
 {
     LaunchSet set;
+    // (which beams come together is known only now)
+    std::vector<MatrixUse> uses;
+    std::vector<DedispPlan> plans;
+    for (const Active &a : f.chunks) {
+        if (!a.has_snr) continue;
+        const SBeam &b = *a.rq.b;
+        uses.push_back({&b.info, b.stride, b.L, b.automatic ? nullptr : &b.tiles});
+        plans.push_back(b.dp);
+    }
+    use_matrix_together(uses, &plans);
+    size_t next = 0;
     for (Active &a : f.chunks) {
         SBeam &b = *a.rq.b;
         const int cur = (int)(a.rq.seq & 1);
@@ -280,8 +292,9 @@ amber_status enqueue(amber_server *s, Flight &f, hipStream_t stream)
         float *snr = reinterpret_cast<float *>(static_cast<char *>(a.block) + b.res_off);
         int32_t *peak = reinterpret_cast<int32_t *>(snr + b.widths.size() * (size_t)b.info.n_dm);
         const int64_t j0 = a.t_first - (a.rq.seq * b.L - b.D);  // first column of a non-negative time
-        set.add_dedisperse(b.dp, make_dedisp_job(b.dp, b.d_delays, b.info.n_dm, n_chan, b.d_in[cur], b.stride, dd,
-                                                 b.dd_stride, b.L));
+        const DedispPlan &dp = plans[next++];
+        set.add_dedisperse(dp, make_dedisp_job(dp, b.d_delays, b.info.n_dm, n_chan, b.d_in[cur], b.stride, dd,
+                                               b.dd_stride, b.L));
         set.add_integrate_snr(b.bp, b.tiles, b.widths.data(), (int)b.widths.size(),
                               make_box_job(dd + j0, b.info.n_dm, b.dd_stride, a.n_out, snr, peak));
     }
@@ -584,7 +597,7 @@ amber_status amber_server_add_beam(amber_server *s, const amber_stream_beam *bm,
     b->D = b->info.max_delay;
     b->stride = round_up(b->D + b->L, 128);
     if ((st = check_stage_stride(b->dp, b->stride)) != AMBER_OK) return st;
-    use_matrix(b->info, b->stride, b->L, bm->tiles == nullptr, true, &b->dp);
+    b->automatic = bm->tiles == nullptr;
     b->dd_stride = round_up(b->L, 64);
     b->res_off = round_up((int64_t)b->info.n_dm * b->dd_stride * 4, 256);
     b->res_bytes = (int64_t)n_widths * b->info.n_dm * 8;
