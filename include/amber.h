@@ -360,9 +360,10 @@ amber_status amber_snr(const int32_t *d_box, int32_t n_dm, int64_t box_stride, i
  * FP64.  Longer rows take the chunked kernel of amber_integrate.
  * tiles == NULL: the defaults, with snr_threads 64 when n_dm >= 4096 (with
  * that many rows one wavefront per row keeps the CUs busiest), else 128,
- * doubled up to 512 while all rows have fewer than 2560 wavefronts, and raised
- * while 16 * snr_threads < twice the largest width rounded up to 16.  A batch with automatic tiles applies the same rule to its total
- * number of rows. */
+ * doubled up to 512 while all rows have fewer than 2560 wavefronts (from 1600 on
+ * only while each has 512 samples or more), and raised while 16 * snr_threads <
+ * twice the largest width rounded up to 16.  A batch with automatic tiles
+ * applies the same rule to its total number of rows and its longest row. */
 amber_status amber_integrate_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_stride, int64_t n_out,
                                  const int32_t *widths, int32_t n_widths,
                                  float *d_snr, int32_t *d_peak_t,
@@ -393,7 +394,8 @@ amber_status amber_downsample(const int32_t *d_dd, int32_t n_dm, int64_t dd_stri
  * Factor 1 is the S/N of the series itself.  FP64 moments as in amber_snr.
  * snr_threads / 64 wavefronts (at most 8) share a row, each sweeping a span of
  * it once for all factors (rows of 2^29 samples or more: the chunks of
- * amber_downsample); tiles == NULL chooses them by the number of rows.
+ * amber_downsample); tiles == NULL chooses them by the rows' number and length
+ * and the number of factors.
  * d_snr: device float [n_factors][n_dm]; d_peak_t: int32 [n_factors][n_dm] or
  * NULL.  Errors as amber_integrate_snr. */
 amber_status amber_downsample_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_stride, int64_t n_out,

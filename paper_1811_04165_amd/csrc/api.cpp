@@ -51,26 +51,41 @@ amber_status hip_fail(hipError_t err, const char *what)
     return fail(AMBER_E_DEVICE, "%s: %s", what, hipGetErrorString(err));
 }
 
-int row_threads(int64_t rows)
+namespace {
+// 2560 wavefronts or more keep the CUs' loads in flight; more per row than that
+// cost more at the row's end than they bring.
+int row_threads(int64_t rows) { return rows >= 4096 ? 64 : 128; }
+bool more_wavefronts(int64_t rows, int t) { return t < 512 && rows * (t / kWave) < 2560; }
+}  // namespace
+
+int auto_dec_threads(int64_t rows, int64_t n_out, int n_factors)
 {
-    // 2560 wavefronts or more keep the CUs' loads in flight; more per
-    // row than that cost more at the row's end than they bring.  Decimated S/N,
-    // ladder of 10 factors, us at 64 / 128 / 256 / 512: 256 rows x 8192 samples
+    // Ladder of 10 factors, us at 64 / 128 / 256 / 512: 256 rows x 8192 samples
     // 30 / 20 / 15 / 15, 771 x 9001 35 / 25 / 23 / 35, 1024 x 24576
     // 85 / 53 / 42 / 51, 2048 x 12208 53 / 40 / 47 / 70, 8192 x 4096
     // 56 / 67 / 91 / 194.
-    int t = rows >= 4096 ? 64 : 128;
-    while (t < 512 && rows * (t / kWave) < 2560) t *= 2;
+    // The statistics of more than 12 factors leave two wavefronts per SIMD, 2048
+    // on the chip, and take a wavefront half as long as 12208 samples do: 16
+    // factors, 2048 rows 158 us at 64 work-items, 211 at 128; 3000 rows 277, 238.
+    if (n_factors > 12 && rows > 1024 && rows <= 2048) return kWave;
+    // a wavefront takes whole chunks of 1024 samples (300 rows x 1200 samples, 16
+    // factors: 40 us at 512, 23 at 128)
+    int t = row_threads(rows);
+    while (more_wavefronts(rows, t) && n_out > 1024 * (t / kWave)) t *= 2;
     return t;
 }
 
-int auto_snr_threads(int64_t rows, const int32_t *widths, int n_widths)
+int auto_snr_threads(int64_t rows, int64_t n_out, const int32_t *widths, int n_widths)
 {
-    // row_threads' rule; sliding widths 1 .. 64, us at 128 / 256 / 512:
+    // sliding widths 1 .. 64, us at 128 / 256 / 512:
     // 256 rows x 8192 samples 16 / 13 / 13, 771 x 9001 21 / 21 / 25,
     // 1024 x 24576 38 / 34 / 38, 2048 x 12208 36 / 39 / 51; widths 1 .. 1024:
     // 26 / 20 / 19, 36 / 35 / 44, 60 / 58 / 66, 65 / 70 / 94
+    // Less than two blocks of 256 samples per wavefront only where these are few:
+    // 1200 samples, widths 1 .. 64 and 10 uneven ones: 64 rows 15.6 / - / 15.0 and
+    // 21.5 / - / 19.8, 1000 rows 16.9 / 17.5 / - and 26.4 / 27.4 / -
     int t = row_threads(rows);
+    while (more_wavefronts(rows, t) && (rows * (t / kWave) < 1600 || n_out >= 512 * (2 * t / kWave))) t *= 2;
     int maxw = 1;
     for (int k = 0; k < n_widths; ++k) maxw = widths[k] > maxw ? widths[k] : maxw;
     const int halo = (maxw + 15) / 16 * 16;
@@ -480,7 +495,7 @@ amber_status amber_integrate_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_s
     if (!d_snr) return fail(AMBER_E_ARG, "d_snr is NULL");
     amber_tiles t = tiles ? *tiles : default_tiles();
     if (!tiles && widths && n_widths >= 1 && n_widths <= AMBER_MAX_WIDTHS)
-        t.snr_threads = auto_snr_threads(n_dm, widths, n_widths);
+        t.snr_threads = auto_snr_threads(n_dm, n_out, widths, n_widths);
     BoxcarPlan plan;
     if ((s = plan_boxcar(t, widths, n_widths, n_out, &plan)) != AMBER_OK) return s;
     return launch_integrate_snr(plan, t, d_dd, n_dm, dd_stride, n_out, widths, n_widths, d_snr, d_peak_t,
@@ -520,7 +535,7 @@ amber_status amber_downsample_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_
     if ((s = downsample_tiles(tiles, factors, n_factors, &t)) != AMBER_OK) return s;
     BoxcarPlan plan;
     if ((s = plan_boxcar(t, factors, n_factors, n_out, &plan, kMaxFactor)) != AMBER_OK) return s;
-    if (!tiles) plan.dec_threads = row_threads(n_dm);
+    if (!tiles) plan.dec_threads = auto_dec_threads(n_dm, n_out, n_factors);
     return launch_integrate_snr(plan, t, d_dd, n_dm, dd_stride, n_out, factors, n_factors, d_snr, d_peak,
                                 (hipStream_t)stream, 1);
 }

@@ -72,8 +72,12 @@ amber_status amber_batch_create(const amber_beam *beams, int32_t n_beams, const 
     // automatic tiles: the boxcar / S/N rows of every beam share launches, so
     // their work-group size follows the batch's total row count
     int64_t total_rows = 0;
-    for (int k = 0; k < n_beams; ++k) total_rows += beams[k].info.n_dm;
-    const int snr_threads = auto_snr_threads(total_rows, widths, n_widths);
+    int64_t longest = 0;
+    for (int k = 0; k < n_beams; ++k) {
+        total_rows += beams[k].info.n_dm;
+        longest = std::max(longest, beams[k].n_out);
+    }
+    const int snr_threads = auto_snr_threads(total_rows, longest, widths, n_widths);
     std::vector<amber_tiles> ts(n_beams);
     std::vector<DedispPlan> dps(n_beams);
     for (int k = 0; k < n_beams; ++k) {

@@ -117,12 +117,15 @@ amber_status plan_boxcar(const amber_tiles &t, const int32_t *widths, int32_t n_
 
 const amber_tiles &default_tiles();
 // Work-group size of the fused boxcar / S/N kernel when the caller passes no
-// tiles: 64 from 4096 rows up (one row per work-group: enough rows keep the
-// CUs busy with single-wave groups), else the default 128; raised while a
-// chunk of 16 samples per work-item is shorter than twice the largest width.
-// Work-items per row for kernels whose wavefronts share a row.
-int row_threads(int64_t rows);
-int auto_snr_threads(int64_t rows, const int32_t *widths, int n_widths);
+// tiles: 64 from 4096 rows up, else 128; doubled up to 512 while all rows have
+// fewer than 2560 wavefronts and each would have two blocks of 256 samples (with
+// fewer than 1600, whatever they have); raised while a chunk of 16 samples per
+// work-item is shorter than twice the largest width.
+int auto_snr_threads(int64_t rows, int64_t n_out, const int32_t *widths, int n_widths);
+// Work-items per row of the decimated S/N: the same without that raise, while
+// each wavefront has a chunk of 1024 samples; 64 for 1025 to 2048 rows of more
+// than 12 factors.
+int auto_dec_threads(int64_t rows, int64_t n_out, int n_factors);
 
 // One beam's dedispersion work: the arguments of a launch, or one entry of a
 // batched launch's job table (tiles of job j occupy work-groups
