@@ -447,20 +447,20 @@ __device__ __forceinline__ void wave_sync_lds()
 }
 
 // Raw samples of one lane in one block (block b: samples 256 b + 4 lane ..
-// + 3).  VEC (16-byte aligned rows of >= 4 samples): one 16-byte load from an
-// in-bounds address; a lane whose 4 samples are not all inside [0, n_out)
-// loads the row's first 16 bytes instead and re-reads its samples one by one
-// when the block is consumed.  Otherwise four dword loads from clamped
-// addresses.  Loads go through global-address-space pointers: flat loads
-// would also count against the LDS counter, and the compiler would then
-// drain every load in flight at each LDS wait.  Indices are 32-bit: the
-// launcher takes rows of fewer than 2^30 samples.
+// + 3).  VEC (16-byte aligned rows of >= 4 samples): one 16-byte load; in the
+// block at the row's end a lane whose 4 samples are not all in the row re-reads
+// them one by one when the block is consumed.  Otherwise four dword loads.
+// Plain loads go through global-address-space pointers: flat loads would also
+// count against the LDS counter, and the compiler would then drain every load in
+// flight at each LDS wait.  Indices are 32-bit: the launcher takes rows of fewer
+// than 2^29 samples.
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) int32_t g_i32;
 typedef const __attribute__((address_space(1))) i32x4 g_i4;
 
 // Buffer loads: a row is a buffer of n_out dwords whose reads past its end
-// return zero (the hardware's range check), so no load needs its address
+// return zero (the hardware's range check, dword by dword: a 16-byte load that
+// straddles the end returns what lies in the row), so no load needs its address
 // clamped and the offsets are a fixed per-lane part plus a scalar block part.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const int32_t *row, int n_out)
 {
@@ -1177,7 +1177,8 @@ __device__ __forceinline__ void dec_load(__amdgpu_buffer_rsrc_t rs, int s0, int 
 #pragma unroll
     for (int q = 0; q < kDecBlocks; ++q) {
         const int blk = s0 / kSpanBlk + q;
-        // (a 16-byte load that straddles the row's end would return nothing)
+        // (16-byte loads over the row's end too would return the same, and
+        // measured 1 % slower: 2048 rows x 12208 samples 41.3 us against 40.9)
         if (VEC && (blk + 1) * kSpanBlk <= n_out)
             x[q] = span_load<true>(rs, blk, lane);
         else
@@ -1467,8 +1468,7 @@ BoxJob make_box_job(const int32_t *d_dd, int n_dm, int64_t dd_stride, int64_t n_
     j.snr = d_snr;
     j.peak = d_peak;
     j.n_dm = n_dm;
-    // 16-byte row loads: aligned rows, and at least 4 samples (the span kernel
-    // reads a row's first 16 bytes in place of a load past its end)
+    // 16-byte row loads: aligned rows, and at least 4 samples
     j.vec_ok = (dd_stride % 4 == 0) && (((uintptr_t)d_dd & 15) == 0) && n_out >= 4;
     j.row_start = 0;
     return j;
