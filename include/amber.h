@@ -95,10 +95,10 @@ typedef struct {
  *   boxcar_step[k]     consecutive outputs per work-item for width k of the
  *                      boxcar / S/N kernels (nrItemsD0, one per width as the
  *                      paper has one per downsampling factor); 1, 2, 4 or 8.
- *                      Used by decimation and by the materialised boxcar /
- *                      S/N; the fused kernel for sliding widths reads every
- *                      width from one prefix per 4 outputs and has no such
- *                      gene (the value must still be valid)
+ *                      Used by the fused kernels for rows of 2^29 samples or
+ *                      more; the others take 4 outputs together (or, where the
+ *                      rows are written, one) and have no such gene (the value
+ *                      must still be valid)
  *   dms_per_thread     DM trials per wavefront (nrDMsPerThread): 1 or 2 (2
  *                      with samples_per_thread <= 16); 0 reads as 1.  A
  *                      work-group covers dms_per_block * dms_per_thread DMs,
@@ -379,10 +379,9 @@ amber_status amber_integrate_snr(const int32_t *d_dd, int32_t n_dm, int64_t dd_s
  * int32 while f * 255 * n_chan < 2^31.
  * factors: host [n_factors], 1 <= f <= min(n_out, 4096), n_factors <= 16.
  * d_y:     device int32 [n_factors][n_dm][y_stride], y_stride >= n_out / min f.
- * tiles:   snr_threads and boxcar_step[k] (one per factor, as the paper has
- *          one gene per downsampling factor) are used; NULL = defaults with
- *          snr_threads raised until 16 * snr_threads >= 2 * round16(max f)
- *          and boxcar_step 1 for every factor. */
+ * tiles:   snr_threads is used (boxcar_step[k], one per factor, must be valid);
+ *          NULL = defaults with snr_threads raised until 16 * snr_threads >=
+ *          2 * round16(max f). */
 amber_status amber_downsample(const int32_t *d_dd, int32_t n_dm, int64_t dd_stride, int64_t n_out,
                               const int32_t *factors, int32_t n_factors, int32_t *d_y, int64_t y_stride,
                               const amber_tiles *tiles, void *stream);
@@ -480,9 +479,11 @@ typedef int32_t (*amber_fitness_fn)(const amber_tiles *tiles, void *user, double
  * samples_per_thread {4 .. 32}, dms_per_block {1 .. 16}, channel_unroll
  * {1 .. 32} (powers of two), dms_per_thread {1, 2}, direct_reads {0, 1},
  * snr_threads {64 .. 1024}, boxcar_step {1, 2, 4, 8} per width, or the
- * single value 8 when the fused kernel for up to 8 sliding widths of at most
- * 64 samples serves these widths (it has no step gene).  Invalid
- * combinations stay in the arrays; the searches skip them. */
+ * single value 8 for up to 8 widths of at most 64 samples.  (Rows below 2^29
+ * samples take kernels without steps whatever their widths: with more or wider
+ * ones the four values make equal configurations, and a caller who sets one
+ * saves evaluations.)  Invalid combinations stay in the arrays; the searches
+ * skip them. */
 amber_status amber_default_space(const amber_delay_info *info, const int32_t *widths, int32_t n_widths,
                                  int64_t n_out, amber_tune_space *space);
 

@@ -30,8 +30,11 @@ void LaunchSet::add_integrate_snr(const BoxcarPlan &p, const amber_tiles &t, con
 {
     auto same = [&](const BGroup &g) {
         if (g.tiles.snr_threads != t.snr_threads || (int)g.widths.size() != n_widths) return false;
+        // (the kernels for sliding widths have no steps but where rows are too
+        // long for the sweep over spans)
+        const bool steps = !span_wide_applies(widths, n_widths, 0, j.n_out);
         for (int w = 0; w < n_widths; ++w)
-            if (g.widths[w] != widths[w] || g.tiles.boxcar_step[w] != t.boxcar_step[w]) return false;
+            if (g.widths[w] != widths[w] || (steps && g.tiles.boxcar_step[w] != t.boxcar_step[w])) return false;
         return true;
     };
     auto it = std::find_if(b_.begin(), b_.end(), same);

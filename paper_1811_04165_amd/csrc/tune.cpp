@@ -873,8 +873,9 @@ amber_status amber_default_space(const amber_delay_info *info, const int32_t *wi
         {64, 128, 256, 512, 1024},  // snr_threads
     };
     sp->n_genes = kGeneBox0 + n_widths;
-    // the kernel for up to 8 sliding widths of at most 64 samples has no
-    // per-width step: those genes keep one value
+    // the kernels for rows below 2^29 samples have no per-width step: those genes
+    // keep one value for up to 8 widths of at most 64 samples (the other spaces
+    // keep the values that callers know)
     const std::vector<int> steps = span_snr_applies(widths, n_widths, 0, n_out) ? std::vector<int>{8}
                                                                                : std::vector<int>{1, 2, 4, 8};
     for (int i = 0; i < sp->n_genes; ++i) {
