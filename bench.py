@@ -1288,9 +1288,10 @@ def main() -> int:
     k1_avg = statistics.mean(k1_ms)
     ops = float(g.n_chan) * samples
     achieved = ops / (k1_avg / 1e3) / 1e12
-    traffic = measured_traffic(ops)
-    # explicit tiles of other than 32 trials run on the vector units
+    # explicit tiles of other than 32 trials run on the vector units, which the
+    # traffic record does not describe
     matrix = tiles.dms_per_block * tiles.dms_per_thread == 32 and not tiles.direct_reads
+    traffic = measured_traffic(ops) if matrix else None
     alu_peak = MATRIX_PEAK_TOPS if matrix else ALU_PEAK_TOPS
     # LDS: on the matrix cores, 32 trials x 32 channels x 64 columns stage 2 KiB,
     # read 6 KiB of operands and add 8 KiB of results; the other kernel reads
