@@ -133,7 +133,7 @@ struct SBeam {
     int maxw = 0;
     amber_tiles tiles{};
     bool automatic = true;        // the tiles are the library's choice
-    DedispPlan dp{};
+    DedispPlan dp{}, alone{};     // the tiles' plan, and the faster one for the beam's chunk alone
     BoxcarPlan bp{};
     int64_t dd_stride = 0;        // int32 per dedispersed row of a chunk block
     int64_t res_off = 0;          // byte offset of the S/N table in a chunk block
@@ -275,7 +275,10 @@ amber_status enqueue(amber_server *s, Flight &f, hipStream_t stream)
         uses.push_back({&b.info, b.stride, b.L, b.automatic ? nullptr : &b.tiles});
         plans.push_back(b.dp);
     }
-    use_matrix_together(uses, &plans);
+    if (f.chunks.size() == 1 && !plans.empty())
+        plans[0] = f.chunks[0].rq.b->alone;
+    else
+        use_matrix_together(uses, &plans);
     size_t next = 0;
     for (Active &a : f.chunks) {
         SBeam &b = *a.rq.b;
@@ -598,6 +601,8 @@ amber_status amber_server_add_beam(amber_server *s, const amber_stream_beam *bm,
     b->stride = round_up(b->D + b->L, 128);
     if ((st = check_stage_stride(b->dp, b->stride)) != AMBER_OK) return st;
     b->automatic = bm->tiles == nullptr;
+    b->alone = b->dp;
+    use_matrix(b->info, b->stride, b->L, b->automatic, &b->alone);
     b->dd_stride = round_up(b->L, 64);
     b->res_off = round_up((int64_t)b->info.n_dm * b->dd_stride * 4, 256);
     b->res_bytes = (int64_t)n_widths * b->info.n_dm * 8;
