@@ -606,9 +606,8 @@ __device__ __forceinline__ void regroup(Tile &k, int base, int next, int window,
     // those of the window's groups as they are: the mean of the ones looked at
     int here = 0;
     for (int w = k.row0 >> 10; 1024 * w < end; ++w) {
-        const int from = max(k.row0 / kGroup - 32 * w, 0);
-        here += __builtin_popcount(*lds<lds_u>(base + kAside + 4 * w) >> from << from &
-                                   (end - 1024 * w >= 1024 ? 0xffffffffu : (1u << ((end - 1024 * w + kGroup - 1) / kGroup)) - 1u));
+        const int from = max(k.row0 / kGroup - 32 * w, 0), to = min((end + kGroup - 1) / kGroup - 32 * w, 32);
+        here += __builtin_popcount(*lds<lds_u>(base + kAside + 4 * w) >> from << from & 0xffffffffu >> (32 - to));
     }
     const int seen = *lds<lds_i>(next + kAsidePasses);
     const bool sort = 5 * passes * (seen >> 16) < 4 * (seen & 0xffff) * here;
