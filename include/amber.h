@@ -116,7 +116,8 @@ typedef struct {
  * samples_per_thread is 16, 2 when it is 32 or when it is 16 with two DMs per
  * wavefront); direct reads use no LDS.
  *
- * Brute-force dedispersion of 256 or more channels whose neighbours move
+ * Brute-force dedispersion of 256 or more channels in DM steps fine enough that
+ * neighbouring channels (in order of frequency; they may be listed in any) move
  * nearly alike runs on the matrix cores, 32 DMs per work-group: always with
  * automatic tiles, and also with tiles of 32 DMs (dms_per_block *
  * dms_per_thread) that stage through LDS (in a batch, and among chunks that the
