@@ -845,9 +845,19 @@ int xcd_remap_setting()
 // the table's summary that only the speed depends on.)
 //
 // A group's columns are its tile's and omax / 2 more on average, which counts
-// where large shifts leave the LDS short rows.  512 x 8192 and 2048 x 2048, by
-// `most` times (1 + omax / 2 / longest row): 21-36 1.2-1.6, 40 (1536 channels)
-// 1.0-1.8, 33 (1024 channels) 1.0-1.2, 45 0.9-1.0, 57 0.7-0.8; so: up to 42.
+// where large shifts leave the LDS short rows: the more the more rounds of 256
+// work-groups there are, as each reads a window of its own.  With `most` times
+// (1 + omax / 2 / longest row), steps of 2 pc/cm3, vector kernel's time over this
+// one's for ascending / descending frequencies:
+//
+//   channels  weighted   41 x 2860, 64 x 8192   400 x 12000, 1000 x 3000   1024 x 12208
+//   1536        40       1.7-1.8 / 1.04         1.45 / 1.3-1.4             0.92 / 0.92
+//   1347        44       1.4-1.6 / 1.0          1.25 / 1.2                 0.79 / 0.77
+//   1152        50       1.25-1.35 / 0.99       1.06 / 1.0                 0.67 / 0.65
+//   1024        56       1.1-1.2 / 0.9          0.96 / 0.9                 0.60 / 0.58
+//
+// so: any up to two rounds, up to 51 to four, else up to 38 (33, 1024 channels:
+// 1.0-1.25).
 //
 // The estimate holds for channels in order of frequency at 1250-1550 MHz.  Wide
 // bands have more remainders at their bottom than it says, other orders before
@@ -877,7 +887,10 @@ void use_matrix(const amber_delay_info &info, int64_t in_stride, int64_t n_out, 
     if (info.n_chan < 256 || most > 18) return;
     // the longest rows that the LDS holds
     const int64_t longest = (kMaxLdsBytes - matrix_lds_bytes(0, (int)omax)) / (4 * kRows);
-    if (longest < 128 || most * (1.0 + 0.5 * (double)omax / (double)longest) > 42.0) return;
+    if (longest < 128) return;
+    const int64_t blocks = (int64_t)((info.n_dm + kRows - 1) / kRows) * ((n_out + longest - 1) / longest);
+    const double weighted = most * (1.0 + 0.5 * (double)omax / (double)longest);
+    if (blocks > 512 && weighted > (blocks > 1024 ? 38.0 : 51.0)) return;
     // remainders per pass: more take registers (and reads) that a band with
     // fewer does not need; one pass of 12 takes less than two of 7
     const int mat = most < 5.1 ? 5 : most < 7.1 ? 7 : most < 9.1 ? 9 : 12;
